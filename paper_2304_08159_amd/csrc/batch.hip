@@ -43,7 +43,7 @@ struct BatchRes {
     double rel;
 };
 
-__device__ void solve_one(const BatchReq& q, BatchRes& res, CoarseLds& S) {
+__device__ void solve_one(const BatchReq& q, BatchRes& res, WgLds& S) {
     const BatchLevel& F = q.lev[0];
     const int nlev = q.nlev;
     const double w = q.omega;
@@ -100,7 +100,8 @@ __device__ void solve_one(const BatchReq& q, BatchRes& res, CoarseLds& S) {
             break;
         }
         if (nlev == 1) {
-            coarse_cg_block<double>(F.g, C, 0, F.b, x, 1e-10, N + 64, S);
+            coarse_cg_wg<double>(F.g, F.L[0], F.L[1], F.L[2], F.Lc, 0, F.b, x, 1e-10, N + 64, S.cg);
+            __syncthreads();
         } else {
             wg_sweep<double, XM_PLAIN>(F, XAccess<double, XM_PLAIN>{x1}, F.b, w, x, false, red);
             wg_restrict<double>(F, x, F.b, q.lev[1]);
@@ -123,7 +124,7 @@ __device__ void solve_one(const BatchReq& q, BatchRes& res, CoarseLds& S) {
 // Mixed precision (see wg_solve_mixed): the FP32 coefficients of every level
 // from the request's FP64 ones, the projected right-hand side, then the
 // defect-correction loop.
-__device__ void solve_one_mixed(const BatchReq& q, BatchRes& res, CoarseLds& S) {
+__device__ void solve_one_mixed(const BatchReq& q, BatchRes& res, WgLds& S) {
     const BatchLevel& F = q.lev[0];
     wg_coeffs32(F, q.lev32, q.nlev);
     const double b2 = wg_project_rhs(F, q.b_in, S.red);
@@ -148,7 +149,7 @@ __device__ void solve_one_mixed(const BatchReq& q, BatchRes& res, CoarseLds& S) 
 __global__ __launch_bounds__(kBatchThreads) void k_poisson_batch(const BatchReq* __restrict__ reqs,
                                                                  int count, unsigned* head,
                                                                  BatchRes* __restrict__ res) {
-    __shared__ CoarseLds S;
+    __shared__ WgLds S;
     __shared__ int take;
     for (;;) {
         if (threadIdx.x == 0) take = int(atomicAdd(head, 1u));

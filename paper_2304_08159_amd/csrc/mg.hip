@@ -1146,273 +1146,6 @@ __global__ __launch_bounds__(1024) void k_reduce(const double* __restrict__ part
     }
 }
 
-// Coarsest level: the iteration of coarse_cg_regs (CG on -A over the active
-// cells, mean-free right-hand side and result, FP64) with one cell per thread
-// (N <= blockDim <= 1024).  Each thread builds its cell's stencil once (the
-// diagonal, six face coefficients and six neighbour slots, a missing
-// neighbour being the cell itself with the coefficient the generic solver
-// uses), so an iteration is six LDS reads of the search direction, two
-// fixed-order sums (one barrier each, alternating buffers) and the barrier
-// after the direction update.  The sums run over the first nw waves (those
-// that can own a cell: every wave of the workgroup executes each barrier, so
-// a larger workgroup, as in the V-cycle tail, gets the same sums bitwise).
-// sp: kCoarseMax doubles of LDS, red: 2 x 16 of LDS.
-template <typename T>
-__device__ void coarse_cg_regs(const Grid& g, const T* L0, const T* L1, const T* L2, T Lc,
-                                int uniform, const T* b, T* xout, double tol, int maxit, int nw,
-                                double* sp, double (*red)[16]) {
-    const int N = int(cells(g));
-    const int t = int(threadIdx.x);
-    const bool own = t < N;
-    auto wsum = [&](double v, int buf) -> double {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        if ((t & 63) == 0 && (t >> 6) < nw) red[buf][t >> 6] = v;
-        __syncthreads();
-        double s = 0.0;
-        for (int w = 0; w < nw; ++w) s += red[buf][w];
-        return s;
-    };
-    double D = 0.0, cf[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    int nb[6] = {t, t, t, t, t, t};
-    if (own) {
-        const int i = t % g.n0, j = (t / g.n0) % g.n1, k = t / (g.n0 * g.n1);
-        const int n[3] = {g.n0, g.n1, g.n2}, per[3] = {g.per0, g.per1, g.per2};
-        const int co[3] = {i, j, k}, st[3] = {1, g.n0, g.n0 * g.n1};
-        const T* Ld[3] = {L0, L1, L2};
-        for (int d = 0; d < g.ndim; ++d) {
-            const int lo = nb_lo(co[d], n[d], per[d]), up = nb_up(co[d], n[d], per[d]);
-            nb[2 * d] = t + (lo - co[d]) * st[d];
-            nb[2 * d + 1] = t + (up - co[d]) * st[d];
-            const double Ll = uniform ? double(Lc) : double(Ld[d][t]);
-            const double Lu = (co[d] < n[d] - 1 || per[d])
-                                  ? (uniform ? double(Lc) : double(Ld[d][nb[2 * d + 1]]))
-                                  : 0.0;
-            cf[2 * d] = Ll;
-            cf[2 * d + 1] = Lu;
-            D += Ll + Lu;
-        }
-    }
-    const bool act = D > 0.0;
-    const double bt = own ? double(b[t]) : 0.0;
-    // mean of b over the active cells
-    const double sumb = wsum(act ? bt : 0.0, 0);
-    const double cnt = wsum(act ? 1.0 : 0.0, 1);
-    const double mean = cnt > 0.0 ? sumb / cnt : 0.0;
-    // solve M x = B with M = -A, B = -(b - mean) on active cells
-    const double B = act ? -(bt - mean) : 0.0;
-    double x = 0.0, r = B, p = B;
-    if (own) sp[t] = p;
-    double rr = wsum(B * B, 0);  // its barrier also publishes sp
-    const double rr0 = rr;
-    if (rr0 > 0.0) {
-        for (int it = 0; it < maxit; ++it) {
-            double Mp = 0.0;
-            if (act) {
-                Mp = D * p;
-#pragma unroll
-                for (int m = 0; m < 6; ++m) Mp -= cf[m] * sp[nb[m]];
-            }
-            const double pq = wsum(p * Mp, 1);
-            if (!(pq > 0.0)) break;
-            const double alpha = rr / pq;
-            x += alpha * p;
-            r -= alpha * Mp;
-            const double rn = wsum(r * r, 0);
-            if (rn <= tol * tol * rr0) break;
-            const double beta = rn / rr;
-            rr = rn;
-            p = r + beta * p;
-            if (own) sp[t] = p;
-            __syncthreads();
-        }
-    }
-    // mean-free result on the active cells (the barrier keeps the last
-    // sum's buffer until every wave has read it)
-    __syncthreads();
-    const double xs = wsum(act ? x : 0.0, 1);
-    const double xm = cnt > 0.0 ? xs / cnt : 0.0;
-    if (own) xout[t] = act ? T(x - xm) : T(0);
-}
-
-// Coarsest level of at most kCgWaveMax cells in one wave: the same CG as
-// coarse_cg_regs with lane l owning cells l, l + 64, ... (PER of them), the
-// stencils in registers and the search direction in LDS (sp, wave-
-// synchronous: one wave writes and reads it).  Every rounding is spelled out
-// (contraction off, fused multiply-adds written as such), so the standalone
-// kernel and the V-cycle tail, which both call it, agree bit for bit.  Sums:
-// per lane over its cells in order, then wave_sum_f64.
-constexpr int kCgWaveMax = 256;
-
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's LDS traffic done
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Data-parallel move of a double across the lanes of a row (CTRL: a DPP
-// control, every lane valid).
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-    const long long u = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, int(u), CTRL, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, int(u >> 32), CTRL, 0xf, 0xf, false);
-    return __longlong_as_double((static_cast<long long>(hi) << 32) |
-                                static_cast<long long>(static_cast<unsigned>(lo)));
-}
-
-__device__ __forceinline__ double readlane_f64(double v, int lane) {
-    const long long u = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane(int(u), lane);
-    const int hi = __builtin_amdgcn_readlane(int(u >> 32), lane);
-    return __longlong_as_double((static_cast<long long>(hi) << 32) |
-                                static_cast<long long>(static_cast<unsigned>(lo)));
-}
-
-// Sum over the 64 lanes of a full wave, the same value in every lane: lane
-// pairs, quads, half rows and rows by data-parallel moves (each add takes
-// two equal partial sums in either order, so every lane of a row ends with
-// the same bits), then the four row sums in row order.
-__device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma clang fp contract(off)
-    v = v + dpp_f64<0xB1>(v);   // quad_perm [1, 0, 3, 2]
-    v = v + dpp_f64<0x4E>(v);   // quad_perm [2, 3, 0, 1]
-    v = v + dpp_f64<0x141>(v);  // row_half_mirror
-    v = v + dpp_f64<0x140>(v);  // row_mirror
-    return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
-}
-
-template <typename T, int PER>
-__device__ void coarse_cg_wave(const Grid& g, const T* L0, const T* L1, const T* L2, T Lc,
-                               int uniform, const T* b, T* xout, double tol, int maxit,
-                               double* sp) {
-#pragma clang fp contract(off)
-    const int N = int(cells(g));
-    const int lane = int(threadIdx.x) & 63;
-    double D[PER], cf[PER][6], x[PER], r[PER], p[PER], Mp[PER], bt[PER];
-    int nb[PER][6];
-    bool act[PER], own[PER];
-#pragma unroll
-    for (int m = 0; m < PER; ++m) {
-        const int c = lane + 64 * m;
-        own[m] = c < N;
-        D[m] = 0.0;
-        bt[m] = 0.0;
-#pragma unroll
-        for (int f = 0; f < 6; ++f) {
-            cf[m][f] = 0.0;
-            nb[m][f] = own[m] ? c : 0;
-        }
-        if (own[m]) {
-            const int i = c % g.n0, j = (c / g.n0) % g.n1, k = c / (g.n0 * g.n1);
-            const int n[3] = {g.n0, g.n1, g.n2}, per[3] = {g.per0, g.per1, g.per2};
-            const int co[3] = {i, j, k}, st[3] = {1, g.n0, g.n0 * g.n1};
-            const T* Ld[3] = {L0, L1, L2};
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                if (d >= g.ndim) break;
-                const int lo = nb_lo(co[d], n[d], per[d]), up = nb_up(co[d], n[d], per[d]);
-                nb[m][2 * d] = c + (lo - co[d]) * st[d];
-                nb[m][2 * d + 1] = c + (up - co[d]) * st[d];
-                const double Ll = uniform ? double(Lc) : double(Ld[d][c]);
-                const double Lu = (co[d] < n[d] - 1 || per[d])
-                                      ? (uniform ? double(Lc) : double(Ld[d][nb[m][2 * d + 1]]))
-                                      : 0.0;
-                cf[m][2 * d] = Ll;
-                cf[m][2 * d + 1] = Lu;
-                D[m] = D[m] + (Ll + Lu);
-            }
-            bt[m] = double(b[c]);
-        }
-        act[m] = D[m] > 0.0;
-    }
-    auto wsum = [&](const double (&v)[PER]) -> double {
-        double s = v[0];
-#pragma unroll
-        for (int m = 1; m < PER; ++m) s = s + v[m];
-        return wave_sum_f64(s);
-    };
-    double t0[PER], t1[PER];
-#pragma unroll
-    for (int m = 0; m < PER; ++m) {
-        t0[m] = act[m] ? bt[m] : 0.0;
-        t1[m] = act[m] ? 1.0 : 0.0;
-    }
-    const double sumb = wsum(t0), cnt = wsum(t1);
-    const double mean = cnt > 0.0 ? sumb / cnt : 0.0;
-    // solve M x = B with M = -A, B = -(b - mean) on active cells
-#pragma unroll
-    for (int m = 0; m < PER; ++m) {
-        const double B = act[m] ? -(bt[m] - mean) : 0.0;
-        x[m] = 0.0;
-        r[m] = B;
-        p[m] = B;
-        if (own[m]) sp[lane + 64 * m] = B;
-        t0[m] = B * B;
-    }
-    double rr = wsum(t0);
-    const double rr0 = rr;
-    wave_lds_sync();
-    if (rr0 > 0.0) {
-        for (int it = 0; it < maxit; ++it) {
-#pragma unroll
-            for (int m = 0; m < PER; ++m) {
-                double v = 0.0;
-                if (act[m]) {
-                    v = D[m] * p[m];
-#pragma unroll
-                    for (int f = 0; f < 6; ++f) v = fma(-cf[m][f], sp[nb[m][f]], v);
-                }
-                Mp[m] = v;
-                t0[m] = p[m] * v;
-            }
-            const double pq = wsum(t0);
-            if (!(pq > 0.0)) break;
-            const double alpha = rr / pq;
-#pragma unroll
-            for (int m = 0; m < PER; ++m) {
-                x[m] = fma(alpha, p[m], x[m]);
-                r[m] = fma(-alpha, Mp[m], r[m]);
-                t0[m] = r[m] * r[m];
-            }
-            const double rn = wsum(t0);
-            if (rn <= tol * tol * rr0) break;
-            const double beta = rn / rr;
-            rr = rn;
-            wave_lds_sync();  // every lane has read sp
-#pragma unroll
-            for (int m = 0; m < PER; ++m) {
-                p[m] = fma(beta, p[m], r[m]);
-                if (own[m]) sp[lane + 64 * m] = p[m];
-            }
-            wave_lds_sync();
-        }
-    }
-    // mean-free result on the active cells
-#pragma unroll
-    for (int m = 0; m < PER; ++m) t0[m] = act[m] ? x[m] : 0.0;
-    const double xm = cnt > 0.0 ? wsum(t0) / cnt : 0.0;
-#pragma unroll
-    for (int m = 0; m < PER; ++m)
-        if (own[m]) xout[lane + 64 * m] = act[m] ? T(x[m] - xm) : T(0);
-}
-
-// The one-wave solve for the level's size (PER = cells per lane, at most
-// MAXPER).
-template <typename T, int MAXPER>
-__device__ __forceinline__ void coarse_cg_wave_any(const Grid& g, const T* L0, const T* L1,
-                                                   const T* L2, T Lc, int uniform, const T* b,
-                                                   T* xout, double tol, int maxit, double* sp) {
-    const int N = int(cells(g));
-    if (N <= 64)
-        coarse_cg_wave<T, 1>(g, L0, L1, L2, Lc, uniform, b, xout, tol, maxit, sp);
-    else if (MAXPER < 4 || N <= 128)
-        coarse_cg_wave<T, 2>(g, L0, L1, L2, Lc, uniform, b, xout, tol, maxit, sp);
-    else
-        coarse_cg_wave<T, 4>(g, L0, L1, L2, Lc, uniform, b, xout, tol, maxit, sp);
-}
-
 // Coarsest level by its inverse (non-uniform levels of at most kDirectMax
 // cells).  On the active cells (D > 0) M = -A is singular with the constant
 // as null vector (per connected set of active cells); M + a 1 1^T, a = (mean D) /
@@ -1524,8 +1257,8 @@ __global__ __launch_bounds__(1024) void k_coarse_inverse(Grid g, Coeffs<T> C, in
 }
 
 // x = G B on the coarsest level in one wave, B the mean-free right-hand side
-// (as coarse_cg_wave forms it), then the mean of x over the active cells
-// removed.  Sums as in coarse_cg_wave; sp: LDS for N doubles.
+// (as coarse_cg forms it), then the mean of x over the active cells
+// removed.  Sums as in coarse_cg; sp: LDS for N doubles.
 template <typename T, int PER>
 __device__ void coarse_direct_wave(const Grid& g, const T* L0, const T* L1, const T* L2, T Lc,
                                    int uniform, const T* b, T* xout, const double* G,
@@ -1609,39 +1342,30 @@ __device__ void coarse_direct_wave(const Grid& g, const T* L0, const T* L1, cons
         if (own[m]) xout[lane + 64 * m] = act[m] ? T(x[m] - xm) : T(0);
 }
 
-// The coarsest solve of a one-wave level: the inverse when it is valid, else
-// the CG.
-template <typename T, int MAXPER>
-__device__ __forceinline__ void coarse_wave_solve(const Grid& g, const T* L0, const T* L1,
-                                                  const T* L2, T Lc, int uniform, const T* b,
-                                                  T* xout, double tol, int maxit, double* sp,
-                                                  const double* G, const int* ok) {
-    const int N = int(cells(g));
-    if (G && N <= 64 && *ok) {
-        coarse_direct_wave<T, 1>(g, L0, L1, L2, Lc, uniform, b, xout, G, sp);
+// The coarsest solve (every thread of the workgroup, or the first wave of one
+// on levels of at most kCgWaveMax cells): the inverse where it is valid, else
+// the iteration.  No barrier at the end.
+template <typename T>
+__device__ __forceinline__ void coarse_solve_wg(const Grid& g, const T* L0, const T* L1,
+                                                const T* L2, T Lc, int uniform, const T* b,
+                                                T* xout, double tol, int maxit, const double* G,
+                                                const int* ok, CgLds& S) {
+    if (G && int(cells(g)) <= 64 && *ok) {
+        if (threadIdx.x < 64)
+            coarse_direct_wave<T, 1>(g, L0, L1, L2, Lc, uniform, b, xout, G, S.u);
         return;
     }
-    coarse_cg_wave_any<T, MAXPER>(g, L0, L1, L2, Lc, uniform, b, xout, tol, maxit, sp);
+    coarse_cg_wg<T>(g, L0, L1, L2, Lc, uniform, b, xout, tol, maxit, S);
 }
 
+// The coarsest solve in a launch of its own: one wave, or 64 kCgGroupWaves
+// threads on levels of more than kCgWaveMax cells.
 template <typename T>
-__global__ __launch_bounds__(64) void k_coarse_cg_wave(Grid g, Coeffs<T> C, int uniform,
-                                                       const T* __restrict__ b,
-                                                       T* __restrict__ xout, double tol,
-                                                       int maxit, const double* G,
-                                                       const int* ok) {
-    __shared__ double sp[kCgWaveMax];
-    coarse_wave_solve<T, 4>(g, C.L0, C.L1, C.L2, C.Lc, uniform, b, xout, tol, maxit, sp, G, ok);
-}
-
-template <typename T>
-__global__ __launch_bounds__(1024) void k_coarse_cg(Grid g, Coeffs<T> C, int uniform,
-                                                    const T* __restrict__ b, T* __restrict__ xout,
-                                                    double tol, int maxit) {
-    __shared__ double sp[kCoarseMax];
-    __shared__ double red[2][16];
-    coarse_cg_regs<T>(g, C.L0, C.L1, C.L2, C.Lc, uniform, b, xout, tol, maxit,
-                      int(blockDim.x) >> 6, sp, red);
+__global__ __launch_bounds__(64 * kCgGroupWaves) void k_coarse_solve(
+    Grid g, Coeffs<T> C, int uniform, const T* __restrict__ b, T* __restrict__ xout, double tol,
+    int maxit, const double* G, const int* ok) {
+    __shared__ CgLds S;
+    coarse_solve_wg<T>(g, C.L0, C.L1, C.L2, C.Lc, uniform, b, xout, tol, maxit, G, ok, S);
 }
 
 // ------------------------------------------------- V-cycle tail, one workgroup
@@ -1656,16 +1380,15 @@ __global__ __launch_bounds__(1024) void k_coarse_cg(Grid g, Coeffs<T> C, int uni
 // into x1, the residual of x1 (kept in x0, free until the post-smoothing)
 // summed into the coarse right-hand side, and on the way up the in-place
 // prolongation into x1 and two sweeps back into x1; the coarsest level is
-// coarse_cg_wave, run by the first wave.  Each cell's arithmetic is that of
+// coarse_solve_wg.  Each cell's arithmetic is that of
 // k_smooth, k_resid_restrict (resid_row and the same sum order over the 2^d
-// children), k_prolong and k_coarse_cg, so the result is bitwise that of
+// children), k_prolong and k_coarse_solve, so the result is bitwise that of
 // the per-level launches.  Face coefficients are read from global memory
 // (L1 / L2).
 constexpr int kTailLevels = 8;
 constexpr int kTailThreads = 1024;
 constexpr int kTailPer = 4;                               // cells per thread and level
 constexpr int kTailLdsCells = kTailThreads * kTailPer * 4 / 3 + 64;  // all levels, 2D included
-constexpr int kTailCgMax = 128;  // coarsest level: two cells per lane
 
 template <typename T>
 struct TailLevel {
@@ -1871,7 +1594,7 @@ template <typename T, bool UNIF, bool D3>
 __global__ __launch_bounds__(kTailThreads) void k_vcycle_tail(TailArgs<T> A) {
     // per level: x0, x1 and b, level after level
     __shared__ T lds[3 * kTailLdsCells];
-    __shared__ double sp[kTailCgMax];
+    __shared__ CgLds cg;
     const int n = A.n;
     auto X0 = [&](int l) -> T* { return lds + A.lev[l].ox0; };
     auto X1 = [&](int l) -> T* { return lds + A.lev[l].ox1; };
@@ -1893,10 +1616,10 @@ __global__ __launch_bounds__(kTailThreads) void k_vcycle_tail(TailArgs<T> A) {
     }
     // coarsest: the first wave; each level's corrected iterate then lands in
     // its x0 (the top level's in global memory)
-    if (threadIdx.x < 64) {
+    {
         const TailLevel<T>& C = A.lev[n - 1];
-        coarse_wave_solve<T, 2>(C.g, C.L0, C.L1, C.L2, C.Lc, UNIF ? 1 : 0, Bv(n - 1), X0(n - 1),
-                                A.tol, int(cells(C.g)) + 64, sp, A.G, A.ok);
+        coarse_solve_wg<T>(C.g, C.L0, C.L1, C.L2, C.Lc, UNIF ? 1 : 0, Bv(n - 1), X0(n - 1), A.tol,
+                           int(cells(C.g)) + 64, A.G, A.ok, cg);
     }
     __syncthreads();
     for (int l = n - 2; l >= 0; --l) {
@@ -2457,16 +2180,10 @@ static wl_status coarse_solve(const Hierarchy<T>& h, const Level<T>& L, T* xout,
         set_error("internal: coarsest level larger than the one-workgroup solver");
         return WL_ERR_INVALID_ARG;
     }
-    if (N <= kCgWaveMax) {
-        const bool dir = h.cinv_set && &L == &h.lev[h.nlev - 1];
-        k_coarse_cg_wave<T><<<1, 64, 0, s>>>(L.g, coeffs_of(L), L.uniform, L.b, xout, h.coarse_tol,
-                                             maxit, dir ? h.cinv : nullptr,
-                                             dir ? h.cinv_ok : nullptr);
-    } else {
-        const unsigned nt = unsigned((N + 63) / 64 * 64);
-        k_coarse_cg<T><<<1, nt, 0, s>>>(L.g, coeffs_of(L), L.uniform, L.b, xout, h.coarse_tol,
-                                        maxit);
-    }
+    const bool dir = h.cinv_set && &L == &h.lev[h.nlev - 1];
+    k_coarse_solve<T><<<1, N <= kCgWaveMax ? 64 : 64 * kCgGroupWaves, 0, s>>>(
+        L.g, coeffs_of(L), L.uniform, L.b, xout, h.coarse_tol, maxit, dir ? h.cinv : nullptr,
+        dir ? h.cinv_ok : nullptr);
     WL_CHECK_LAUNCH();
     return WL_OK;
 }
@@ -2474,13 +2191,13 @@ static wl_status coarse_solve(const Hierarchy<T>& h, const Level<T>& L, T* xout,
 // First level of the V-cycle tail (k_vcycle_tail), 0 for none: with fused
 // kernels on (wl_set_fused_sweeps) and the Jacobi smoother, the first level
 // below the fine one of at most tail_cells() cells, provided at least one
-// smoothed level lies above the coarsest, the coarsest fits the one-wave
+// smoothed level lies above the coarsest, the coarsest fits the one-workgroup
 // solve and the levels fit the tail's LDS.
 template <typename T>
 static int tail_level(const Hierarchy<T>& h) {
     const size_t lim = std::min(tail_cells(), size_t(kTailThreads) * kTailPer);
     if (h.pairs == 0 || h.smoother != 0 || h.nlev < 3 || lim == 0) return 0;
-    if (cells(h.lev[h.nlev - 1].g) > size_t(kTailCgMax)) return 0;
+    if (cells(h.lev[h.nlev - 1].g) > size_t(kCoarseMax)) return 0;
     for (int l = 1; l < h.nlev - 1; ++l) {
         if (cells(h.lev[l].g) > lim) continue;
         const int lt = std::max(l, h.nlev - kTailLevels);

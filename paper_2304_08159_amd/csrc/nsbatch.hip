@@ -163,7 +163,7 @@ __device__ void wg_outflow(const NsReq& q, const float* ue_x, const float* out_e
 // the pressure-gradient update into out (coef = c dt).  Returns the solve's
 // status; adds its V-cycles to *vc.
 __device__ int wg_project_stage(const NsReq& q, double coef, float* const out[3], int* vc,
-                                CoarseLds& S) {
+                                WgLds& S) {
     const Grid& g = q.g;
     const int N = int(cells(g));
     const int per[3] = {g.per0, g.per1, g.per2};
@@ -225,7 +225,7 @@ __device__ int wg_project_stage(const NsReq& q, double coef, float* const out[3]
     return status;
 }
 
-__device__ void run_one(const NsReq& q, NsRes& res, CoarseLds& S) {
+__device__ void run_one(const NsReq& q, NsRes& res, WgLds& S) {
     const Grid& g = q.g;
     const int N = int(cells(g));
     // geometry of the body (at rest): moments, FP64 coefficients, FP32 levels
@@ -277,7 +277,7 @@ __device__ void run_one(const NsReq& q, NsRes& res, CoarseLds& S) {
 
 __global__ __launch_bounds__(kNsThreads) void k_ns_batch(const NsReq* __restrict__ reqs, int count,
                                                          unsigned* head, NsRes* __restrict__ res) {
-    __shared__ CoarseLds S;
+    __shared__ WgLds S;
     __shared__ int take;
     for (;;) {
         if (threadIdx.x == 0) take = int(atomicAdd(head, 1u));

@@ -20,6 +20,13 @@ struct WgLevel {
     int uniform;  // all faces Lc, fully periodic
 };
 
+// LDS of a workgroup that owns whole hierarchies: the coarsest solve's and
+// the sums'.
+struct WgLds {
+    CgLds cg;
+    double red[16];
+};
+
 __device__ __forceinline__ void wg_coords(const Grid& g, int c, int& i, int& j, int& k) {
     i = c % g.n0;
     const int q = c / g.n0;
@@ -148,7 +155,7 @@ __device__ void wg_coarsen(const WgLevel<T>& F, const WgLevel<T>& Cl) {
 // the minimum-norm coarsest solve, then the prolongation and two plain
 // sweeps.
 template <typename T>
-__device__ void wg_vcycle_tail(const WgLevel<T>* lev, int n, T w, double coarse_tol, CoarseLds& S) {
+__device__ void wg_vcycle_tail(const WgLevel<T>* lev, int n, T w, double coarse_tol, WgLds& S) {
     for (int l = 0; l < n - 1; ++l) {
         const WgLevel<T>& L = lev[l];
         wg_sweep<T, XM_ZERO>(L, XAccess<T, XM_ZERO>{nullptr}, L.b, w, L.x[0], false,
@@ -157,8 +164,9 @@ __device__ void wg_vcycle_tail(const WgLevel<T>* lev, int n, T w, double coarse_
         wg_restrict<T>(L, L.x[1], L.b, lev[l + 1]);
     }
     const WgLevel<T>& Cst = lev[n - 1];
-    coarse_cg_block<T>(Cst.g, wg_coeffs(Cst), Cst.uniform, Cst.b, Cst.x[1], coarse_tol,
-                       int(cells(Cst.g)) + 64, S);
+    coarse_cg_wg<T>(Cst.g, Cst.L[0], Cst.L[1], Cst.L[2], Cst.Lc, Cst.uniform, Cst.b, Cst.x[1],
+                    coarse_tol, int(cells(Cst.g)) + 64, S.cg);
+    __syncthreads();
     for (int l = n - 2; l >= 0; --l) {
         const WgLevel<T>& L = lev[l];
         const WgLevel<T>& C = lev[l + 1];

@@ -57,11 +57,12 @@ __device__ inline void wg_coeffs32(const WgLevel<double>& F, const WgLevel<float
 // One FP32 V-cycle on lev[0..n) for A e = lev[0].b from the iterate in
 // lev[0].x[1] (zero: from e = 0), result in lev[0].x[1].
 __device__ inline void wg_vcycle32(const WgLevel<float>* lev, int n, float w, bool zero,
-                                   CoarseLds& S) {
+                                   WgLds& S) {
     const WgLevel<float>& L0 = lev[0];
     if (n == 1) {
-        coarse_cg_block<float>(L0.g, wg_coeffs(L0), L0.uniform, L0.b, L0.x[1], 1e-6,
-                               int(cells(L0.g)) + 64, S);
+        coarse_cg_wg<float>(L0.g, L0.L[0], L0.L[1], L0.L[2], L0.Lc, L0.uniform, L0.b, L0.x[1], 1e-6,
+                            int(cells(L0.g)) + 64, S.cg);
+        __syncthreads();
         return;
     }
     if (zero) {
@@ -84,7 +85,7 @@ __device__ inline void wg_vcycle32(const WgLevel<float>* lev, int n, float w, bo
 // *vcycles gets the inner V-cycles run, *r2 the last ||r||^2.
 __device__ inline int wg_solve_mixed(const WgLevel<double>& F, const WgLevel<float>* lev, int nlev,
                                      float w, double tol2, double abs_r2, int max_vcycles,
-                                     CoarseLds& S, int* vcycles, double* r2_out) {
+                                     WgLds& S, int* vcycles, double* r2_out) {
     double* x = F.x[0];
     const int N = int(cells(F.g));
     const Coeffs<double> C = wg_coeffs(F);

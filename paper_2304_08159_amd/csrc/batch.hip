@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "wl_internal.h"
+#include "wl_ressolve.h"
 #include "wl_wg.h"
 #include "wl_wgsolve.h"
 
@@ -32,11 +33,23 @@ struct BatchReq {
     double tol, omega;
     int max_vcycles;
     int mixed;                            // FP32 inner V-cycles, FP64 outer
+    int kind;                             // general path (0) or which resident one
     const double* b_in;
-    BatchLevel lev[kMaxLevels];           // mixed: only the fine level (FP64 x, b, L)
-    WgLevel<float> lev32[kMaxLevels];     // mixed: the FP32 hierarchy
+    double* x;                            // resident path: solution, projected right-hand side
+    double* b;
+    union {
+        struct {
+            BatchLevel lev[kMaxLevels];        // mixed: only the fine level (FP64 x, b, L)
+            WgLevel<float> lev32[kMaxLevels];  // mixed: the FP32 hierarchy
+        };
+        ResPlan64 p64;
+        ResPlan32 p32;
+    };
 };
-
+// the request table is part of the footprint: the resident plans must not grow it
+static_assert(sizeof(ResPlan64) <= sizeof(BatchLevel) * kMaxLevels + sizeof(WgLevel<float>) * kMaxLevels &&
+                  sizeof(ResPlan32) <= sizeof(BatchLevel) * kMaxLevels + sizeof(WgLevel<float>) * kMaxLevels,
+              "resident plan larger than the general one");
 
 struct BatchRes {
     int status, vcycles;
@@ -144,8 +157,45 @@ __device__ void solve_one_mixed(const BatchReq& q, BatchRes& res, WgLds& S) {
     __syncthreads();
 }
 
-// Persistent kernel: each workgroup takes the next request from the queue
-// until none is left (every workgroup reaches the exit).
+// A request on the resident path (wl_ressolve.h).
+template <bool D3, bool MIXED>
+__device__ __forceinline__ void solve_resident(const BatchReq& q, BatchRes& res, WgLds& S,
+                                               ResLds& R) {
+    int st = WL_OK, k = 0;
+    double rel = 0.0;
+    if (MIXED) {
+        const ResPlan32& P = q.p32;
+        const RLevel<double>& F = P.fine;
+        // FP32 coefficients of the fine level, the classes of both
+        for (int c = int(threadIdx.x); c < F.N; c += int(blockDim.x)) {
+            const_cast<float*>(P.lev[0].Lx)[c] = float(F.Lx[c]);
+            if (D3) const_cast<float*>(P.lev[0].Ly)[c] = float(F.Ly[c]);
+            const_cast<float*>(P.lev[0].Lw)[c] = float(F.Lw[c]);
+        }
+        R.cws[F.ocw + int(threadIdx.x)] = res_classify<double, D3, RS_SEQ>(F, 1.0);
+        __syncthreads();
+        res_setup<float, D3, RS_SEQ>(P.lev, P.n, float(q.omega), reinterpret_cast<float*>(R.raw), R.cws);
+        const double b2 = res_project(F, R.cws, q.b_in, q.b, S.red);
+        if (b2 == 0.0) {
+            for (int c = int(threadIdx.x); c < F.N; c += int(blockDim.x)) q.x[c] = 0.0;
+            __syncthreads();
+        } else {
+            double r2 = 0.0;
+            st = res_solve_mixed<D3>(P, float(q.omega), q.x, q.b, q.tol * q.tol * b2,
+                                     q.max_vcycles, S, R, &k, &r2);
+            rel = sqrt(r2 / b2);
+        }
+    } else {
+        res_solve64<D3>(q.p64, q.omega, q.b_in, q.x, q.b, q.tol, q.max_vcycles, S, R, &st, &k, &rel);
+    }
+    if (threadIdx.x == 0) res = BatchRes{st, k, rel};
+    __syncthreads();
+}
+
+// Persistent kernels: each workgroup takes the next request from the queue
+// until none is left (every workgroup reaches the exit).  One kernel per kind
+// of request keeps each within its registers (all kinds in one: 686 registers
+// spilled).
 __global__ __launch_bounds__(kBatchThreads) void k_poisson_batch(const BatchReq* __restrict__ reqs,
                                                                  int count, unsigned* head,
                                                                  BatchRes* __restrict__ res) {
@@ -162,6 +212,79 @@ __global__ __launch_bounds__(kBatchThreads) void k_poisson_batch(const BatchReq*
         else
             solve_one(reqs[r], res[r], S);
     }
+}
+
+template <bool D3, bool MIXED>
+__global__ __launch_bounds__(kBatchThreads) void k_poisson_resident(
+    const BatchReq* __restrict__ reqs, int count, unsigned* head, BatchRes* __restrict__ res) {
+    __shared__ WgLds S;
+    __shared__ ResLds R;
+    __shared__ int take;
+    for (;;) {
+        if (threadIdx.x == 0) take = int(atomicAdd(head, 1u));
+        __syncthreads();
+        const int r = take;
+        __syncthreads();
+        if (r >= count) return;
+        solve_resident<D3, MIXED>(reqs[r], res[r], S, R);
+    }
+}
+
+// Kinds of request, each served by a kernel of its own.
+enum { kGeneral = 0, kRes2 = 1, kRes2Mixed = 2, kRes3 = 3, kRes3Mixed = 4, kKinds = 5 };
+
+// The resident plan of a request whose general one is in q (its scratch
+// arrays serve both: the sweep buffers, which the resident path does not need,
+// hold w / D).  Taken when the fine level splits into segments of at most 16
+// cells (up to 16,384 cells) and the levels fit the LDS; 256 requests of 128^2 in
+// FP64 then take 2.17 instead of 4.31 ms, 200 of 192 x 64 in FP32 with FP64
+// correction 1.6 instead of 4.1 ms.  Larger fine levels do not fit the LDS and
+// keep the general path.
+void plan_resident(BatchReq& q) {
+    const int nlev = q.nlev;
+    if (nlev < 2 || nlev > kResLevels) return;
+    const BatchLevel& F = q.lev[0];
+    const bool d3 = F.g.ndim == 3;
+    auto level = [&](auto& out, const auto& L, double Lc, bool last) {
+        using V = std::remove_const_t<std::remove_pointer_t<decltype(out.Lx)>>;
+        const V* Lp[3] = {L.L[0], L.L[1], L.L[2]};
+        return res_plan_level<V>(L.g, Lp, V(Lc), V(0), kBatchThreads, kResRows, last, out);
+    };
+    int ncls = 0;
+    double* x = F.x[0];
+    double* b = F.b;
+    double Lc = 1.0;
+    if (q.mixed) {
+        ResPlan32 P{};
+        P.n = nlev;
+        P.gc = q.lev32[nlev - 1].g;
+        if (!level(P.fine, F, 1.0, false)) return;
+        P.fine.ocw = kResThreads * ncls++;
+        for (int l = 0; l < nlev; ++l, Lc *= d3 ? 2.0 : 1.0) {
+            if (!level(P.lev[l], q.lev32[l], Lc, l == nlev - 1)) return;
+            P.lev[l].wd = q.lev32[l].x[0];
+        }
+        if (!res_plan_lds(P.lev, nlev, d3, size_t(P.fine.N) * sizeof(double), ncls)) return;
+        for (int l = 1; l < nlev - 1; ++l)
+            if (P.lev[l].seg > 4) return;
+        q.kind = d3 ? kRes3Mixed : kRes2Mixed;
+        q.p32 = P;
+    } else {
+        ResPlan64 P{};
+        P.n = nlev;
+        P.gc = q.lev[nlev - 1].g;
+        for (int l = 0; l < nlev; ++l, Lc *= d3 ? 2.0 : 1.0) {
+            if (!level(P.lev[l], q.lev[l], Lc, l == nlev - 1)) return;
+            P.lev[l].wd = l == 0 ? q.lev[0].x[1] : q.lev[l].x[0];
+        }
+        if (!res_plan_lds(P.lev, nlev, d3, 0, ncls)) return;
+        for (int l = 1; l < nlev - 1; ++l)
+            if (P.lev[l].seg > 4) return;
+        q.kind = d3 ? kRes3 : kRes2;
+        q.p64 = P;
+    }
+    q.x = x;
+    q.b = b;
 }
 
 // Checks one request and fills its descriptor, carving its level arrays.
@@ -232,6 +355,7 @@ wl_status plan_one(const wl_batch_request& in, Carver& c, BatchReq& q) {
             for (int d = 0; d < 3; ++d) L.L[d] = d < ndim ? c.take<float>(Nl) : nullptr;
             for (int d = 0; d < ndim; ++d) n[d] /= 2;
         }
+        plan_resident(q);
         return WL_OK;
     }
     for (int l = 0; l < nlev; ++l) {
@@ -255,6 +379,7 @@ wl_status plan_one(const wl_batch_request& in, Carver& c, BatchReq& q) {
         }
         for (int d = 0; d < ndim; ++d) n[d] /= 2;
     }
+    plan_resident(q);
     return WL_OK;
 }
 
@@ -265,14 +390,15 @@ struct BatchLayout {
 };
 
 // Checks every request and carves the batch's device arrays from c; with
-// table non-null, also fills the count request descriptors there.
+// table non-null, also fills the count request descriptors there, request r
+// at place[r]; without, place (when given) receives their kinds.
 wl_status plan(const wl_batch_request* reqs, int count, Carver& c, BatchLayout& lay,
-               BatchReq* table) {
+               BatchReq* table, int* place = nullptr) {
     if (count < 0) return set_error("count must be >= 0"), WL_ERR_INVALID_ARG;
     if (count > 0 && !reqs) return set_error("reqs is NULL"), WL_ERR_INVALID_ARG;
     lay.dev_reqs = c.take<BatchReq>(size_t(count > 0 ? count : 1));
     lay.dev_res = c.take<BatchRes>(size_t(count > 0 ? count : 1));
-    lay.dev_head = c.take<unsigned>(1);
+    lay.dev_head = c.take<unsigned>(kKinds);  // within the 256 bytes one took
     for (int r = 0; r < count; ++r) {
         BatchReq q;
         const wl_status st = plan_one(reqs[r], c, q);
@@ -280,7 +406,10 @@ wl_status plan(const wl_batch_request* reqs, int count, Carver& c, BatchLayout& 
             set_error("request " + std::to_string(r) + ": " + last_error_text());
             return st;
         }
-        if (table) table[r] = q;
+        if (table)
+            table[place[r]] = q;
+        else if (place)
+            place[r] = q.kind;
     }
     return WL_OK;
 }
@@ -300,6 +429,7 @@ constexpr int kNoAllocMaxRequests = 256;
 std::mutex g_noalloc_host_mu;
 BatchReq g_noalloc_table[kNoAllocMaxRequests];
 BatchRes g_noalloc_res[kNoAllocMaxRequests];
+int g_noalloc_place[kNoAllocMaxRequests];
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
 
@@ -340,7 +470,8 @@ int compute_units() {
 // queue head, runs the persistent kernel on hip_stream and copies the results
 // back through res (count entries; synchronises).
 wl_status batch_run(const wl_batch_request* reqs, int count, void* workspace, size_t ws_bytes,
-                    void* hip_stream, wl_batch_result* results, BatchReq* table, BatchRes* res) {
+                    void* hip_stream, wl_batch_result* results, BatchReq* table, BatchRes* res,
+                    int* place) {
     if (reinterpret_cast<uintptr_t>(workspace) % 256)
         return set_error("workspace must be 256-byte aligned"), WL_ERR_INVALID_ARG;
     for (int r = 0; r < count && reqs; ++r)
@@ -350,7 +481,7 @@ wl_status batch_run(const wl_batch_request* reqs, int count, void* workspace, si
         }
     Carver need;
     BatchLayout dry;
-    WL_TRY(plan(reqs, count, need, dry, nullptr));
+    WL_TRY(plan(reqs, count, need, dry, nullptr, place));
     if (ws_bytes < need.off) {
         set_error("workspace smaller than wl_poisson_batch_footprint");
         return WL_ERR_OUT_OF_MEMORY;
@@ -358,26 +489,44 @@ wl_status batch_run(const wl_batch_request* reqs, int count, void* workspace, si
     Carver c;
     c.base = static_cast<char*>(workspace);
     BatchLayout lay;
-    WL_TRY(plan(reqs, count, c, lay, table));
+    // the requests of each kind together, in the caller's order
+    int n[kKinds] = {}, start[kKinds], at[kKinds];
+    for (int r = 0; r < count; ++r) ++n[place[r]];
+    for (int k = 0, sum = 0; k < kKinds; sum += n[k++]) start[k] = at[k] = sum;
+    for (int r = 0; r < count; ++r) place[r] = at[place[r]]++;
+    WL_TRY(plan(reqs, count, c, lay, table, place));
     hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
-    // request table and a zero queue head (the no-allocation scratch keeps
-    // the last call's contents, so the head is cleared on every call)
-    const unsigned zero = 0u;
+    // request table and zero queue heads (the no-allocation scratch keeps
+    // the last call's contents, so the heads are cleared on every call)
+    const unsigned zero[kKinds] = {};
     WL_CHECK_HIP(hipMemcpyAsync(lay.dev_reqs, table, sizeof(BatchReq) * size_t(count),
                                 hipMemcpyHostToDevice, s));
-    WL_CHECK_HIP(hipMemcpyAsync(lay.dev_head, &zero, sizeof(zero), hipMemcpyHostToDevice, s));
-    const int grid = std::min(count, compute_units());
-    k_poisson_batch<<<grid, kBatchThreads, 0, s>>>(lay.dev_reqs, count, lay.dev_head, lay.dev_res);
-    WL_CHECK_HIP(hipGetLastError());
+    WL_CHECK_HIP(hipMemcpyAsync(lay.dev_head, zero, sizeof(zero), hipMemcpyHostToDevice, s));
+    for (int k = 0; k < kKinds; ++k) {
+        if (n[k] == 0) continue;
+        const int grid = std::min(n[k], compute_units());
+        const BatchReq* q = lay.dev_reqs + start[k];
+        BatchRes* out = lay.dev_res + start[k];
+        unsigned* head = lay.dev_head + k;
+        switch (k) {
+            case kRes2: k_poisson_resident<false, false><<<grid, kBatchThreads, 0, s>>>(q, n[k], head, out); break;
+            case kRes2Mixed: k_poisson_resident<false, true><<<grid, kBatchThreads, 0, s>>>(q, n[k], head, out); break;
+            case kRes3: k_poisson_resident<true, false><<<grid, kBatchThreads, 0, s>>>(q, n[k], head, out); break;
+            case kRes3Mixed: k_poisson_resident<true, true><<<grid, kBatchThreads, 0, s>>>(q, n[k], head, out); break;
+            default: k_poisson_batch<<<grid, kBatchThreads, 0, s>>>(q, n[k], head, out); break;
+        }
+        WL_CHECK_HIP(hipGetLastError());
+    }
     WL_CHECK_HIP(hipMemcpyAsync(res, lay.dev_res, sizeof(BatchRes) * size_t(count),
                                 hipMemcpyDeviceToHost, s));
     WL_CHECK_HIP(hipStreamSynchronize(s));
     wl_status worst = WL_OK;
     for (int r = 0; r < count; ++r) {
-        results[r].status = res[r].status;
-        results[r].vcycles = res[r].vcycles;
-        results[r].rel_resid = res[r].rel;
-        if (res[r].status != WL_OK && worst == WL_OK) worst = wl_status(res[r].status);
+        const BatchRes& o = res[place[r]];
+        results[r].status = o.status;
+        results[r].vcycles = o.vcycles;
+        results[r].rel_resid = o.rel;
+        if (o.status != WL_OK && worst == WL_OK) worst = wl_status(o.status);
     }
     if (worst == WL_ERR_NOT_CONVERGED) set_error("some batch requests reached max_vcycles");
     if (worst == WL_ERR_NONFINITE) set_error("non-finite residual in a batch request");
@@ -409,8 +558,9 @@ wl_status wl_poisson_batch_solve(const wl_batch_request* reqs, int count, void* 
     if (count < 0) return set_error("count must be >= 0"), WL_ERR_INVALID_ARG;
     std::vector<BatchReq> table(static_cast<size_t>(count));
     std::vector<BatchRes> res(static_cast<size_t>(count));
+    std::vector<int> place(static_cast<size_t>(count));
     return batch_run(reqs, count, workspace, ws_bytes, hip_stream, results, table.data(),
-                     res.data());
+                     res.data(), place.data());
 }
 
 wl_status wl_poisson_batch_solve_noalloc(const wl_batch_request* reqs, int count,
@@ -437,7 +587,7 @@ wl_status wl_poisson_batch_solve_noalloc(const wl_batch_request* reqs, int count
     // fixed host staging (no heap); one call at a time in this process
     std::lock_guard<std::mutex> lock(g_noalloc_host_mu);
     return batch_run(reqs, count, ws, kNoAllocScratchBytes, hip_stream, results, g_noalloc_table,
-                     g_noalloc_res);
+                     g_noalloc_res, g_noalloc_place);
 }
 
 }  // extern "C"

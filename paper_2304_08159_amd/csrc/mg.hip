@@ -21,6 +21,7 @@
 #include "wl_cg.h"
 #include "wl_device.h"
 #include "wl_jacobi.h"
+#include "wl_res.h"
 
 namespace wl {
 
@@ -161,6 +162,9 @@ static size_t pair3_max_cells() {
     return v;
 }
 
+constexpr int kTailPer = 4;           // cells per thread of the V-cycle tail's largest level
+constexpr int kTailGlobalLevels = 3;  // tail levels whose coefficients stay in global memory
+
 // Largest level that the one-workgroup V-cycle tail takes (WL_TAIL_CELLS
 // overrides it; 0 turns the tail off): from 16^3 down, the per-level
 // launches cost more than one workgroup's pass over the level.
@@ -211,6 +215,14 @@ void carve_hierarchy(Carver& c, Hierarchy<T>& h, int ndim, const int n[3], const
     if (h.smoother == 1) {
         const Grid& g0 = h.lev[0].g;
         h.cgpart = c.take<double>(5 * reduce_slots_for(g0));
+    }
+    // w / D and class words of the V-cycle tail's levels
+    if (h.pairs && nlev >= 3) {
+        size_t nt = 0;
+        for (int l = 1; l < nlev - 1; ++l)
+            if (cells(h.lev[l].g) <= size_t(kResThreads) * kTailPer) nt += cells(h.lev[l].g);
+        h.tail_wd = c.take<T>(nt);
+        h.tail_cls = c.take<unsigned>(size_t(kTailGlobalLevels) * kResThreads);
     }
     const size_t Nc = cells(h.lev[nlev - 1].g);
     if (Nc <= size_t(kDirectMax)) {
@@ -1371,263 +1383,67 @@ __global__ __launch_bounds__(64 * kCgGroupWaves) void k_coarse_solve(
 // ------------------------------------------------- V-cycle tail, one workgroup
 // The coarse end of a V-cycle (Sec. 2's GMG on its smallest levels) in one
 // launch: below a few thousand cells every per-level kernel is a handful of
-// waves whose launch costs more than its work.  One workgroup of
-// kTailThreads runs the levels from the first small one down to the
-// coarsest and back up with every iterate and right-hand side in LDS: the
-// top level's right-hand side is read once, its corrected iterate written
-// once, and the steps in between are separated by barriers.  Per level, as
-// the per-level kernels do it: a sweep from zero into x0, a sweep from x0
-// into x1, the residual of x1 (kept in x0, free until the post-smoothing)
-// summed into the coarse right-hand side, and on the way up the in-place
-// prolongation into x1 and two sweeps back into x1; the coarsest level is
-// coarse_solve_wg.  Each cell's arithmetic is that of
-// k_smooth, k_resid_restrict (resid_row and the same sum order over the 2^d
-// children), k_prolong and k_coarse_solve, so the result is bitwise that of
-// the per-level launches.  Face coefficients are read from global memory
-// (L1 / L2).
-constexpr int kTailLevels = 8;
-constexpr int kTailThreads = 1024;
-constexpr int kTailPer = 4;                               // cells per thread and level
-constexpr int kTailLdsCells = kTailThreads * kTailPer * 4 / 3 + 64;  // all levels, 2D included
-
-template <typename T>
-struct TailLevel {
-    Grid g;
-    const T* L0;
-    const T* L1;
-    const T* L2;
-    T Lc;
-    T wD;                      // w / D of a uniform level
-    unsigned long long m0, mc;  // ceil(2^32 / d) for n0 and the column count: exact quotients
-    int parts, seg;             // column walks: z segments per column, planes per segment
-    int ox0, ox1, ob;           // LDS offsets of x0, x1 and b
-};
+// waves whose launch costs more than its work.  One workgroup runs the levels
+// from the first small one down to the coarsest and back up, resident in
+// registers and LDS (wl_res.h): per level a sweep from zero, a sweep, the
+// residual summed into the coarse right-hand side, and on the way up the
+// prolongation and two sweeps; the coarsest level is coarse_solve_wg.  Each
+// cell's arithmetic is that of the per-level kernels, so the result is bitwise
+// that of the per-level launches.
+constexpr int kTailMaxSeg = 8;
+constexpr int kTailElems = 17664;          // LDS elements of the levels (138 KB in FP64)
 
 template <typename T>
 struct TailArgs {
-    TailLevel<T> lev[kTailLevels];
-    const T* b;  // right-hand side of the top tail level
-    T* x;        // its corrected iterate
-    const double* G;  // the coarsest level's inverse and its flag (null: CG)
+    RLevel<T> lev[kResLevels];
+    Grid gc;             // the coarsest level
+    const T* b;          // right-hand side of the top tail level
+    T* x;                // its corrected iterate
+    unsigned* cls;       // class words of the levels that are not staged (RLevel::ocw)
+    const double* G;     // the coarsest level's inverse and its flag (null: CG)
     const int* ok;
-    int n;       // levels: n - 1 smoothed, the last one solved
+    int n;               // levels: n - 1 smoothed, the last one solved
+    int ncls;            // levels with class words
     T omega;
     double tol;
 };
 
-// Column walks: a level of n0 x n1 columns; with fewer columns than
-// threads each column is split into `parts` z segments of `seg` planes and
-// thread t takes column t mod cols, segment t / cols; otherwise thread t
-// takes the whole columns t, t + kTailThreads, ...  fn(col, i, j, k0, k1)
-// walks its cells up z as the tiled kernels do (x / y neighbour offsets
-// fixed along the column, the lower z neighbour carried), so a cell costs
-// little besides its own arithmetic.  Ends with a barrier.
-template <typename T, typename Fn>
-__device__ __forceinline__ void tail_columns(const TailLevel<T>& L, Fn&& fn) {
-    const int t = int(threadIdx.x);
-    const int cols = L.g.n0 * L.g.n1;
-    auto run = [&](int col, int k0, int k1) {
-        const int j = int((unsigned long long)unsigned(col) * L.m0 >> 32);
-        fn(col, col - j * L.g.n0, j, k0, k1);
-    };
-    if (cols >= kTailThreads) {
-        for (int col = t; col < cols; col += kTailThreads) run(col, 0, L.g.n2);
-    } else if (t < L.parts * cols) {
-        const int part = int((unsigned long long)unsigned(t) * L.mc >> 32);
-        const int k0 = part * L.seg;
-        run(t - part * cols, k0, min(L.g.n2, k0 + L.seg));
-    }
-    __syncthreads();
-}
-
-// x / y neighbour offsets of column (i, j) as the tiled kernels form them: a
-// non-periodic boundary points at the cell itself (its face coefficient is
-// zero), a periodic one wraps.
-struct TailCol {
-    int oxm, oxp, oym, oyp;
-    bool hxu, hyu;
-};
-
-__device__ __forceinline__ TailCol tail_col(const Grid& g, int i, int j) {
-    TailCol q;
-    const int ixm = i > 0 ? i - 1 : (g.per0 ? g.n0 - 1 : i);
-    const int ixp = i < g.n0 - 1 ? i + 1 : (g.per0 ? 0 : i);
-    const int jym = j > 0 ? j - 1 : (g.per1 ? g.n1 - 1 : j);
-    const int jyp = j < g.n1 - 1 ? j + 1 : (g.per1 ? 0 : j);
-    q.oxm = ixm - i;
-    q.oxp = ixp - i;
-    q.oym = (jym - j) * g.n0;
-    q.oyp = (jyp - j) * g.n0;
-    q.hxu = i < g.n0 - 1 || g.per0;
-    q.hyu = j < g.n1 - 1 || g.per1;
-    return q;
-}
-
-// Offset of the upper / lower z neighbour of plane k (self at a
-// non-periodic end) and whether the upper face exists.
-__device__ __forceinline__ int tail_zup(const Grid& g, int k, int plane, bool& hzu) {
-    hzu = k < g.n2 - 1 || g.per2;
-    return (k < g.n2 - 1 ? plane : (g.per2 ? -(g.n2 - 1) * plane : 0));
-}
-__device__ __forceinline__ int tail_zlo(const Grid& g, int k, int plane) {
-    return k > 0 ? -plane : (g.per2 ? (g.n2 - 1) * plane : 0);
-}
-
-// Damped-Jacobi sweep of the whole level, x -> xout (ZERO: from x = 0), or
-// (RESID) the residual b - A x into xout; each cell as k_smooth updates it
-// (resid_row as k_resid_restrict forms it).
-template <typename T, bool UNIF, bool D3, bool ZERO, bool RESID>
-__device__ void tail_sweep(const TailLevel<T>& L, const T* __restrict__ x,
-                           const T* __restrict__ b, T omega, T* __restrict__ xout) {
-    const Grid& g = L.g;
-    const int plane = g.n0 * g.n1;
-    tail_columns(L, [&](int col, int i, int j, int k0, int k1) {
-        const TailCol q = tail_col(g, i, j);
-        auto xv = [&](int idx) -> T { return ZERO ? T(0) : x[idx]; };
-        int c = col + k0 * plane;
-        T xI = xv(c), xzl = T(0), Lzl = T(0);
-        if (D3) {
-            xzl = xv(c + tail_zlo(g, k0, plane));
-            if (!UNIF) Lzl = L.L2[c];
-        }
-        for (int k = k0; k < k1; ++k, c += plane) {
-            T xzu = T(0), Lzu = T(0);
-            bool hzu = false;
-            if (D3) {
-                const int cu = c + tail_zup(g, k, plane, hzu);
-                xzu = xv(cu);
-                if (!UNIF) {
-                    Lzu = L.L2[cu];
-                    if (!hzu) Lzu = T(0);
-                }
-            }
-            const T xxl = xv(c + q.oxm), xxu = xv(c + q.oxp);
-            const T xyl = xv(c + q.oym), xyu = xv(c + q.oyp);
-            const T bv = b[c];
-            T Lxl, Lxu, Lyl, Lyu;
-            if (UNIF) {
-                Lxl = Lxu = Lyl = Lyu = L.Lc;
-            } else {
-                Lxl = L.L0[c];
-                Lxu = L.L0[c + q.oxp];
-                Lyl = L.L1[c];
-                Lyu = L.L1[c + q.oyp];
-                if (!q.hxu) Lxu = T(0);
-                if (!q.hyu) Lyu = T(0);
-            }
-            if (RESID) {
-                const T Lz0 = UNIF ? (D3 ? L.Lc : T(0)) : Lzl, Lz1 = UNIF ? (D3 ? L.Lc : T(0)) : Lzu;
-                xout[c] = resid_row(bv, xI, xxl, xxu, xyl, xyu, xzl, xzu, Lxl, Lxu, Lyl, Lyu, Lz0,
-                                    Lz1, D3);
-            } else if (UNIF) {
-                // the sweep of a uniform level: one D, second differences
-                const T Ax = jacobi_ax_uniform(xI, xxl, xxu, xyl, xyu, xzl, xzu, L.Lc, D3);
-                T D = T(0);
-                D += L.Lc + L.Lc;
-                D += L.Lc + L.Lc;
-                if (D3) D += L.Lc + L.Lc;
-                xout[c] = jacobi_new_scaled(xI, bv - Ax, D > T(0), L.wD);
-            } else {
-                T Ax, D;
-                jacobi_terms(xI, xxl, xxu, xyl, xyu, xzl, xzu, Lxl, Lxu, Lyl, Lyu, Lzl, Lzu, D3, Ax,
-                             D);
-                xout[c] = jacobi_new(xI, bv - Ax, D, omega);
-            }
-            xzl = xI;
-            xI = xzu;
-            Lzl = Lzu;
-        }
-    });
-}
-
-// Coarse right-hand side bc from the residual rs of level F: the z pair of
-// each child column summed first, then the x pair, then the y pair (the
-// order of k_resid_restrict).
-template <typename T, bool D3>
-__device__ void tail_restrict_sum(const TailLevel<T>& F, const T* __restrict__ rs,
-                                  const TailLevel<T>& C, T* __restrict__ bc) {
-    const int n0 = F.g.n0, plane = F.g.n0 * F.g.n1, cplane = C.g.n0 * C.g.n1;
-    tail_columns(C, [&](int col, int ic, int jc, int k0, int k1) {
-        const int f0 = 2 * ic + n0 * (2 * jc);
-        for (int kc = k0; kc < k1; ++kc) {
-            const int f = f0 + plane * (D3 ? 2 * kc : kc);
-            auto zs = [&](int o) -> T { return D3 ? rs[f + o] + rs[f + o + plane] : rs[f + o]; };
-            bc[col + kc * cplane] = (zs(0) + zs(1)) + (zs(n0) + zs(n0 + 1));
-        }
-    });
-}
-
-// xout = x + P xc: the coarse correction interpolated onto the level, each
-// coarse plane's x / y interpolation formed once per column walk (the
-// operations of prolong_at).
-template <typename T, bool D3>
-__device__ void tail_prolong(const TailLevel<T>& L, const TailLevel<T>& C,
-                             const T* __restrict__ xc, const T* __restrict__ x,
-                             T* __restrict__ xout) {
-    const Grid& g = L.g;
-    const int plane = g.n0 * g.n1;
-    tail_columns(L, [&](int col, int i, int j, int k0, int k1) {
-        int ip, iq, jp, jq;
-        prolong_pair(i, C.g.n0, g.per0, ip, iq);
-        prolong_pair(j, C.g.n1, g.per1, jp, jq);
-        const int cn0 = C.g.n0, cpl = C.g.n0 * C.g.n1;
-        auto cplane = [&](int K) -> T {
-            const T* r = xc + cpl * K;
-            const T lo = lerp34(r[ip + cn0 * jp], r[iq + cn0 * jp]);
-            const T hi = lerp34(r[ip + cn0 * jq], r[iq + cn0 * jq]);
-            return lerp34(lo, hi);
-        };
-        int c = col + k0 * plane;
-        if (!D3) {
-            xout[c] = x[c] + cplane(0);
-            return;
-        }
-        for (int k = k0; k < k1; ++k, c += plane) {
-            int kp, kq;
-            prolong_pair(k, C.g.n2, g.per2, kp, kq);
-            xout[c] = x[c] + lerp34(cplane(kp), cplane(kq));
-        }
-    });
-}
-
 template <typename T, bool UNIF, bool D3>
-__global__ __launch_bounds__(kTailThreads) void k_vcycle_tail(TailArgs<T> A) {
-    // per level: x0, x1 and b, level after level
-    __shared__ T lds[3 * kTailLdsCells];
+__global__ __launch_bounds__(kResThreads) void k_vcycle_tail(TailArgs<T> A) {
+    __shared__ T lds[kTailElems];
+    __shared__ unsigned cws[kTailGlobalLevels * kResThreads];
     __shared__ CgLds cg;
-    const int n = A.n;
-    auto X0 = [&](int l) -> T* { return lds + A.lev[l].ox0; };
-    auto X1 = [&](int l) -> T* { return lds + A.lev[l].ox1; };
-    auto Bv = [&](int l) -> T* { return lds + A.lev[l].ob; };
+    const int n = A.n, t = int(threadIdx.x);
     {
         const T* __restrict__ bg = A.b;
-        T* __restrict__ b0 = Bv(0);
-        const int N = int(cells(A.lev[0].g));
-        for (int c = int(threadIdx.x); c < N; c += kTailThreads) b0[c] = bg[c];
-        __syncthreads();
+        T* __restrict__ b0 = lds + A.lev[0].ob;
+        for (int c = t; c < A.lev[0].N; c += kResThreads) b0[c] = bg[c];
     }
-    // down: the pre-smoothed iterate stays in x1, x0 takes the residual
-    for (int l = 0; l < n - 1; ++l) {
-        const TailLevel<T>& L = A.lev[l];
-        tail_sweep<T, UNIF, D3, true, false>(L, nullptr, Bv(l), A.omega, X0(l));
-        tail_sweep<T, UNIF, D3, false, false>(L, X0(l), Bv(l), A.omega, X1(l));
-        tail_sweep<T, UNIF, D3, false, true>(L, X1(l), Bv(l), A.omega, X0(l));
-        tail_restrict_sum<T, D3>(L, X0(l), A.lev[l + 1], Bv(l + 1));
-    }
-    // coarsest: the first wave; each level's corrected iterate then lands in
-    // its x0 (the top level's in global memory)
-    {
-        const TailLevel<T>& C = A.lev[n - 1];
-        coarse_solve_wg<T>(C.g, C.L0, C.L1, C.L2, C.Lc, UNIF ? 1 : 0, Bv(n - 1), X0(n - 1), A.tol,
-                           int(cells(C.g)) + 64, A.G, A.ok, cg);
+    if (!UNIF) {
+        for (int l = 0; l < A.ncls; ++l) cws[l * kResThreads + t] = A.cls[l * kResThreads + t];
+        for (int l = 0; l < n - 1; ++l)
+            if (A.lev[l].ol >= 0) res_stage<T, D3, RS_TILED>(A.lev[l], A.omega, lds);
     }
     __syncthreads();
-    for (int l = n - 2; l >= 0; --l) {
-        const TailLevel<T>& L = A.lev[l];
-        tail_prolong<T, D3>(L, A.lev[l + 1], X0(l + 1), X1(l), X0(l));
-        tail_sweep<T, UNIF, D3, false, false>(L, X0(l), Bv(l), A.omega, X1(l));
-        tail_sweep<T, UNIF, D3, false, false>(L, X1(l), Bv(l), A.omega, l == 0 ? A.x : X0(l));
+    for (int l = 0; l < n - 1; ++l)
+        res_down<T, D3, UNIF, kTailMaxSeg, RS_TILED>(A.lev[l], A.lev[l + 1], A.omega, lds, cws);
+    {
+        const RLevel<T>& C = A.lev[n - 1];
+        coarse_solve_wg<T>(A.gc, C.Lx, D3 ? C.Ly : C.Lw, D3 ? C.Lw : nullptr, C.Lc, UNIF ? 1 : 0,
+                           lds + C.ob, lds + C.ox0, A.tol, C.N + 64, A.G, A.ok, cg);
     }
+    __syncthreads();
+    for (int l = n - 2; l >= 0; --l)
+        res_up<T, D3, UNIF, kTailMaxSeg, RS_TILED>(A.lev[l], A.lev[l + 1], A.omega, lds, cws, l == 0 ? A.x : nullptr);
+}
+
+// Class words and w / D of the tail's levels (one workgroup, when the
+// coefficients change).
+template <typename T, bool D3>
+__global__ __launch_bounds__(kResThreads) void k_tail_classes(TailArgs<T> A) {
+    for (int l = 0; l < A.n - 1; ++l)
+        if (A.lev[l].ol < 0)
+            A.cls[A.lev[l].ocw + int(threadIdx.x)] = res_classify<T, D3, RS_TILED>(A.lev[l], A.omega);
 }
 
 // Per-block class of a level for a tiling (see Coeffs::cls): 0 when every
@@ -2188,6 +2004,45 @@ static wl_status coarse_solve(const Hierarchy<T>& h, const Level<T>& L, T* xout,
     return WL_OK;
 }
 
+// The tail's arguments when it starts at level lt; false when the levels do
+// not fit (more columns than threads, LDS, class words).
+template <typename T>
+static bool tail_args(const Hierarchy<T>& h, int lt, TailArgs<T>& A) {
+    A = TailArgs<T>{};
+    A.n = h.nlev - lt;
+    if (A.n < 2 || A.n > kResLevels) return false;
+    A.gc = h.lev[h.nlev - 1].g;
+    A.omega = T(h.omega);
+    A.tol = h.coarse_tol;
+    A.b = h.lev[lt].b;
+    A.x = h.lev[lt].x[1];
+    A.cls = h.tail_cls;
+    A.G = h.cinv_set ? h.cinv : nullptr;
+    A.ok = h.cinv_set ? h.cinv_ok : nullptr;
+    const bool d3 = A.gc.ndim == 3;
+    T* wd = h.tail_wd;
+    for (int t = 0; t < A.n; ++t) {
+        const Level<T>& L = h.lev[lt + t];
+        const T* Lp[3] = {L.L[0], L.L[1], L.L[2]};
+        if (!res_plan_level<T>(L.g, Lp, L.Lc, uniform_wd(L, T(h.omega)), kResThreads, kTailMaxSeg,
+                               t == A.n - 1, A.lev[t]))
+            return false;
+    }
+    const int used = res_layout(A.lev, 0, A.n, 0);
+    if (used > kTailElems) return false;
+    if (!h.lev[lt].uniform) {
+        res_stage_layout(A.lev, 0, A.n, used, kTailElems, d3);
+        for (int t = 0; t < A.n - 1; ++t) {
+            if (A.lev[t].ol >= 0) continue;
+            if (A.ncls == kTailGlobalLevels) return false;
+            A.lev[t].ocw = A.ncls++ * kResThreads;
+            A.lev[t].wd = wd;
+            if (wd) wd += A.lev[t].N;
+        }
+    }
+    return true;
+}
+
 // First level of the V-cycle tail (k_vcycle_tail), 0 for none: with fused
 // kernels on (wl_set_fused_sweeps) and the Jacobi smoother, the first level
 // below the fine one of at most tail_cells() cells, provided at least one
@@ -2195,66 +2050,36 @@ static wl_status coarse_solve(const Hierarchy<T>& h, const Level<T>& L, T* xout,
 // solve and the levels fit the tail's LDS.
 template <typename T>
 static int tail_level(const Hierarchy<T>& h) {
-    const size_t lim = std::min(tail_cells(), size_t(kTailThreads) * kTailPer);
+    const size_t lim = std::min(tail_cells(), size_t(kResThreads) * kTailPer);
     if (h.pairs == 0 || h.smoother != 0 || h.nlev < 3 || lim == 0) return 0;
     if (cells(h.lev[h.nlev - 1].g) > size_t(kCoarseMax)) return 0;
     for (int l = 1; l < h.nlev - 1; ++l) {
         if (cells(h.lev[l].g) > lim) continue;
-        const int lt = std::max(l, h.nlev - kTailLevels);
-        size_t sum = 0;
-        for (int q = lt; q < h.nlev; ++q) sum += cells(h.lev[q].g);
-        return sum <= size_t(kTailLdsCells) ? lt : 0;
+        TailArgs<T> A;
+        for (int lt = std::max(l, h.nlev - kResLevels); lt < h.nlev - 1; ++lt)
+            if (tail_args(h, lt, A)) return lt;
+        return 0;
     }
     return 0;
 }
 
 template <typename T>
-static wl_status vcycle_tail(const Hierarchy<T>& h, int lt, hipStream_t s) {
-    TailArgs<T> A{};
-    A.n = h.nlev - lt;
-    A.omega = T(h.omega);
-    A.tol = h.coarse_tol;
-    A.b = h.lev[lt].b;
-    A.x = h.lev[lt].x[1];
-    A.G = h.cinv_set ? h.cinv : nullptr;
-    A.ok = h.cinv_set ? h.cinv_ok : nullptr;
-    if (A.n < 2 || A.n > kTailLevels) {
-        set_error("internal: V-cycle tail of an unsupported depth");
+static wl_status vcycle_tail(const Hierarchy<T>& h, int lt, hipStream_t s, bool classes = false) {
+    TailArgs<T> A;
+    if (!tail_args(h, lt, A)) {
+        set_error("internal: V-cycle tail of an unsupported depth or size");
         return WL_ERR_INVALID_ARG;
     }
-    const unsigned long long two32 = 1ull << 32;
-    int off = 0;
-    for (int t = 0; t < A.n; ++t) {
-        const Level<T>& L = h.lev[lt + t];
-        TailLevel<T>& D = A.lev[t];
-        D.g = L.g;
-        D.L0 = L.L[0];
-        D.L1 = L.L[1];
-        D.L2 = L.L[2];
-        D.Lc = L.Lc;
-        D.wD = uniform_wd(L, T(h.omega));
-        const int N = int(cells(L.g)), cols = L.g.n0 * L.g.n1;
-        D.m0 = (two32 + unsigned(L.g.n0) - 1) / unsigned(L.g.n0);
-        D.mc = (two32 + unsigned(cols) - 1) / unsigned(cols);
-        int parts = cols >= kTailThreads ? 1 : std::max(1, std::min(L.g.n2, kTailThreads / cols));
-        D.seg = (L.g.n2 + parts - 1) / parts;
-        D.parts = (L.g.n2 + D.seg - 1) / D.seg;
-        D.ox0 = off;
-        D.ox1 = off + N;
-        D.ob = off + 2 * N;
-        off += 3 * N;
-    }
-    if (off > 3 * kTailLdsCells) {
-        set_error("internal: V-cycle tail levels exceed its LDS");
-        return WL_ERR_INVALID_ARG;
-    }
-    const bool d3 = h.lev[lt].g.ndim == 3;
-    if (h.lev[lt].uniform)
-        d3 ? k_vcycle_tail<T, true, true><<<1, kTailThreads, 0, s>>>(A)
-           : k_vcycle_tail<T, true, false><<<1, kTailThreads, 0, s>>>(A);
+    const bool d3 = A.gc.ndim == 3;
+    if (classes)
+        d3 ? k_tail_classes<T, true><<<1, kResThreads, 0, s>>>(A)
+           : k_tail_classes<T, false><<<1, kResThreads, 0, s>>>(A);
+    else if (h.lev[lt].uniform)
+        d3 ? k_vcycle_tail<T, true, true><<<1, kResThreads, 0, s>>>(A)
+           : k_vcycle_tail<T, true, false><<<1, kResThreads, 0, s>>>(A);
     else
-        d3 ? k_vcycle_tail<T, false, true><<<1, kTailThreads, 0, s>>>(A)
-           : k_vcycle_tail<T, false, false><<<1, kTailThreads, 0, s>>>(A);
+        d3 ? k_vcycle_tail<T, false, true><<<1, kResThreads, 0, s>>>(A)
+           : k_vcycle_tail<T, false, false><<<1, kResThreads, 0, s>>>(A);
     WL_CHECK_LAUNCH();
     return WL_OK;
 }
@@ -2279,6 +2104,8 @@ wl_status mg_coarsen_all(Hierarchy<T>& h, hipStream_t s) {
         C.uniform = F.uniform;
         C.Lc = F.Lc * (F.g.ndim == 3 ? T(2) : T(1));
     }
+    if (const int lt = tail_level(h); lt > 0 && !h.lev[lt].uniform)
+        WL_TRY(vcycle_tail(h, lt, s, true));
     // block classes of the non-uniform levels for both tilings
     for (int l = 0; l < h.nlev; ++l) {
         Level<T>& L = h.lev[l];

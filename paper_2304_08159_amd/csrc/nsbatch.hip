@@ -19,6 +19,7 @@
 #include "wl_internal.h"
 #include "wl_ns.h"
 #include "wl_nsdev.h"
+#include "wl_ressolve.h"
 #include "wl_vel.h"
 #include "wl_wg.h"
 #include "wl_wgsolve.h"
@@ -53,7 +54,12 @@ struct NsReq {
     double* sigma;        // projection right-hand side (FP64)
     WgLevel<double> F;    // x[0] = caller pressure (FP64), b = projected sigma, L = FP64 coefficients
     WgLevel<float> lev[kMaxLevels];
+    int kind;             // NsKind: how its pressure solves run
+    ResPlan32 plan;
 };
+
+// Pressure solves on the general path, or resident (wl_ressolve.h) in 2D / 3D.
+enum NsKind { kNsGeneral = 0, kNsRes2 = 1, kNsRes3 = 2, kNsKinds = 3 };
 
 struct NsRes {
     int status, vcycles;
@@ -162,8 +168,9 @@ __device__ void wg_outflow(const NsReq& q, const float* ue_x, const float* out_e
 // the mixed-precision pressure solve (warm-started, relative tolerance) and
 // the pressure-gradient update into out (coef = c dt).  Returns the solve's
 // status; adds its V-cycles to *vc.
-__device__ int wg_project_stage(const NsReq& q, double coef, float* const out[3], int* vc,
-                                WgLds& S) {
+template <int KIND>
+__device__ __forceinline__ int wg_project_stage(const NsReq& q, double coef, float* const out[3], int* vc,
+                                WgLds& S, ResLds* R) {
     const Grid& g = q.g;
     const int N = int(cells(g));
     const int per[3] = {g.per0, g.per1, g.per2};
@@ -194,13 +201,22 @@ __device__ int wg_project_stage(const NsReq& q, double coef, float* const out[3]
         q.sigma[cc] = double(div * scale);
     }
     __syncthreads();
-    const double b2 = wg_project_rhs(q.F, q.sigma, S.red);
+    constexpr bool D3 = KIND == kNsRes3;
+    double b2;
+    if constexpr (KIND == kNsGeneral)
+        b2 = wg_project_rhs(q.F, q.sigma, S.red);
+    else
+        b2 = res_project(q.plan.fine, R->cws, q.sigma, q.F.b, S.red);
     int status = WL_OK;
     if (b2 > 0.0) {
         int k = 0;
         double r2 = 0.0;
-        status = wg_solve_mixed(q.F, q.lev, q.nlev, q.omega, q.tol * q.tol * b2, 0.0,
-                                q.max_vcycles, S, &k, &r2);
+        if constexpr (KIND == kNsGeneral)
+            status = wg_solve_mixed(q.F, q.lev, q.nlev, q.omega, q.tol * q.tol * b2, 0.0,
+                                    q.max_vcycles, S, &k, &r2);
+        else
+            status = res_solve_mixed<D3>(q.plan, q.omega, q.F.x[0], q.F.b, q.tol * q.tol * b2,
+                                         q.max_vcycles, S, *R, &k, &r2);
         *vc += k;
     } else {
         for (int cc = threadIdx.x; cc < N; cc += blockDim.x) q.F.x[0][cc] = 0.0;
@@ -225,7 +241,8 @@ __device__ int wg_project_stage(const NsReq& q, double coef, float* const out[3]
     return status;
 }
 
-__device__ void run_one(const NsReq& q, NsRes& res, WgLds& S) {
+template <int KIND>
+__device__ __forceinline__ void run_one(const NsReq& q, NsRes& res, WgLds& S, ResLds* R) {
     const Grid& g = q.g;
     const int N = int(cells(g));
     // geometry of the body (at rest): moments, FP64 coefficients, FP32 levels
@@ -241,7 +258,16 @@ __device__ void run_one(const NsReq& q, NsRes& res, WgLds& S) {
         }
     }
     __syncthreads();
-    wg_coeffs32(q.F, q.lev, q.nlev);
+    if constexpr (KIND == kNsGeneral) {
+        wg_coeffs32(q.F, q.lev, q.nlev);
+    } else {
+        constexpr bool D3 = KIND == kNsRes3;
+        for (int cc = threadIdx.x; cc < N; cc += blockDim.x)
+            for (int d = 0; d < g.ndim; ++d) q.lev[0].L[d][cc] = float(q.F.L[d][cc]);
+        R->cws[q.plan.fine.ocw + int(threadIdx.x)] = res_classify<double, D3, RS_SEQ>(q.plan.fine, 1.0);
+        __syncthreads();
+        res_setup<float, D3, RS_SEQ>(q.plan.lev, q.plan.n, q.omega, reinterpret_cast<float*>(R->raw), R->cws);
+    }
     double t = 0.0, dt = 0.0;
     int vc = 0, status = WL_OK;
     for (int step = 0; step < q.steps; ++step) {
@@ -251,23 +277,20 @@ __device__ void run_one(const NsReq& q, NsRes& res, WgLds& S) {
             break;
         }
         const float dtf = float(dt);
-        // predictor (c = 1)
-        wg_momentum(q, field(q, q.u, q.uout), q.u, q.f, dtf, false);
-        if (q.outflow) wg_outflow(q, q.u[0], q.uout, q.uout, q.f[0], dtf, false, q.fo, S.red);
-        int st = wg_project_stage(q, dt, q.u1, &vc, S);
-        if (st != WL_OK && status == WL_OK) status = st;
-        if (q.outflow) {
-            for (int p = threadIdx.x; p < g.n1 * g.n2; p += blockDim.x) q.out1[p] = q.fo[p];
-            __syncthreads();
-        }
-        // corrector (c = 1/2)
-        wg_momentum(q, field(q, q.u1, q.out1), q.u, q.f, dtf, true);
-        if (q.outflow) wg_outflow(q, q.u1[0], q.out1, q.uout, q.f[0], dtf, true, q.fo, S.red);
-        st = wg_project_stage(q, 0.5 * dt, q.u, &vc, S);
-        if (st != WL_OK && status == WL_OK) status = st;
-        if (q.outflow) {
-            for (int p = threadIdx.x; p < g.n1 * g.n2; p += blockDim.x) q.uout[p] = q.fo[p];
-            __syncthreads();
+        // predictor (c = 1) into u1 / out1, corrector (c = 1/2) into u / uout
+        for (int corr = 0; corr < 2; ++corr) {
+            float* const* e = corr ? q.u1 : q.u;
+            float* const oe = corr ? q.out1 : q.uout;
+            wg_momentum(q, field(q, e, oe), q.u, q.f, dtf, corr != 0);
+            if (q.outflow) wg_outflow(q, e[0], oe, q.uout, q.f[0], dtf, corr != 0, q.fo, S.red);
+            const int st =
+                wg_project_stage<KIND>(q, corr ? 0.5 * dt : dt, corr ? q.u : q.u1, &vc, S, R);
+            if (st != WL_OK && status == WL_OK) status = st;
+            if (q.outflow) {
+                float* const o = corr ? q.uout : q.out1;
+                for (int p = threadIdx.x; p < g.n1 * g.n2; p += blockDim.x) o[p] = q.fo[p];
+                __syncthreads();
+            }
         }
         t += dt;
     }
@@ -275,9 +298,15 @@ __device__ void run_one(const NsReq& q, NsRes& res, WgLds& S) {
     __syncthreads();
 }
 
+template <int KIND>
 __global__ __launch_bounds__(kNsThreads) void k_ns_batch(const NsReq* __restrict__ reqs, int count,
                                                          unsigned* head, NsRes* __restrict__ res) {
     __shared__ WgLds S;
+    ResLds* R = nullptr;
+    if constexpr (KIND != kNsGeneral) {
+        __shared__ ResLds lds;
+        R = &lds;
+    }
     __shared__ int take;
     for (;;) {
         if (threadIdx.x == 0) take = int(atomicAdd(head, 1u));
@@ -285,13 +314,41 @@ __global__ __launch_bounds__(kNsThreads) void k_ns_batch(const NsReq* __restrict
         const int r = take;
         __syncthreads();
         if (r >= count) return;
-        run_one(reqs[r], res[r], S);
+        run_one<KIND>(reqs[r], res[r], S, R);
     }
 }
 
 wl_status bad(int r, const std::string& msg) {
     set_error("NS request " + std::to_string(r) + ": " + msg);
     return WL_ERR_INVALID_ARG;
+}
+
+// The resident plan of a request's pressure solves (its sweep buffers, which
+// the resident path does not need, hold w / D); taken up to 16 rows per thread
+// (8,192 cells) when the levels fit the LDS: 32 runs of 64^2, 20 steps, 24.5 ms
+// instead of 43.9.  Longer segments would spill the registers that hold them.
+void plan_resident(NsReq& q) {
+    if (q.nlev < 2 || q.nlev > kResLevels) return;
+    const bool d3 = q.g.ndim == 3;
+    ResPlan32 P{};
+    P.n = q.nlev;
+    P.gc = q.lev[q.nlev - 1].g;
+    const double* Lf[3] = {q.F.L[0], q.F.L[1], q.F.L[2]};
+    if (!res_plan_level<double>(q.g, Lf, 1.0, 0.0, kNsThreads, kResRows, false, P.fine)) return;
+    int ncls = 0;
+    P.fine.ocw = kResThreads * ncls++;
+    float Lc = 1.0f;
+    for (int l = 0; l < q.nlev; ++l, Lc *= d3 ? 2.0f : 1.0f) {
+        const float* Lp[3] = {q.lev[l].L[0], q.lev[l].L[1], q.lev[l].L[2]};
+        if (!res_plan_level<float>(q.lev[l].g, Lp, Lc, 0.0f, kNsThreads, kResRows, l == q.nlev - 1,
+                                   P.lev[l]))
+            return;
+        P.lev[l].wd = q.lev[l].x[0];
+        if (l > 0 && l < q.nlev - 1 && P.lev[l].seg > 4) return;
+    }
+    if (!res_plan_lds(P.lev, q.nlev, d3, size_t(P.fine.N) * sizeof(double), ncls)) return;
+    q.plan = P;
+    q.kind = d3 ? kNsRes3 : kNsRes2;
 }
 
 // Checks one request and fills its descriptor, carving its arrays.
@@ -383,6 +440,7 @@ wl_status plan_one(const wl_ns_request& in, int r, Carver& c, NsReq& q) {
         for (int d = 0; d < 3; ++d) L.L[d] = d < ndim ? c.take<float>(Nl) : nullptr;
         for (int d = 0; d < ndim; ++d) n[d] /= 2;
     }
+    plan_resident(q);
     return WL_OK;
 }
 
@@ -392,16 +450,22 @@ struct NsLayout {
     unsigned* dev_head = nullptr;
 };
 
-wl_status plan(const wl_ns_request* reqs, int count, Carver& c, NsLayout& lay, NsReq* table) {
+// With table non-null, request r's descriptor goes to table[place[r]];
+// without, place receives the requests' kinds.
+wl_status plan(const wl_ns_request* reqs, int count, Carver& c, NsLayout& lay, NsReq* table,
+               int* place) {
     if (count < 0) return set_error("count must be >= 0"), WL_ERR_INVALID_ARG;
     if (count > 0 && !reqs) return set_error("reqs is NULL"), WL_ERR_INVALID_ARG;
     lay.dev_reqs = c.take<NsReq>(size_t(count > 0 ? count : 1));
     lay.dev_res = c.take<NsRes>(size_t(count > 0 ? count : 1));
-    lay.dev_head = c.take<unsigned>(1);
+    lay.dev_head = c.take<unsigned>(kNsKinds);  // within the 256 bytes one took
     for (int r = 0; r < count; ++r) {
         NsReq q;
         WL_TRY(plan_one(reqs[r], r, c, q));
-        if (table) table[r] = q;
+        if (table)
+            table[place[r]] = q;
+        else
+            place[r] = q.kind;
     }
     return WL_OK;
 }
@@ -432,7 +496,7 @@ wl_status wl_ns_batch_footprint(const wl_ns_request* reqs, int count, size_t* by
     Carver c;
     c.take<NsReq>(size_t(count > 0 ? count : 1));
     c.take<NsRes>(size_t(count > 0 ? count : 1));
-    c.take<unsigned>(1);
+    c.take<unsigned>(kNsKinds);
     for (int r = 0; r < count; ++r) {
         // the caller's arrays need not exist yet for a footprint query
         wl_ns_request probe = reqs[r];
@@ -454,7 +518,8 @@ wl_status wl_ns_batch_run(const wl_ns_request* reqs, int count, void* workspace,
         return set_error("workspace must be 256-byte aligned"), WL_ERR_INVALID_ARG;
     Carver need;
     NsLayout dry;
-    WL_TRY(plan(reqs, count, need, dry, nullptr));
+    std::vector<int> place(static_cast<size_t>(count));
+    WL_TRY(plan(reqs, count, need, dry, nullptr, place.data()));
     if (ws_bytes < need.off) {
         set_error("workspace smaller than wl_ns_batch_footprint");
         return WL_ERR_OUT_OF_MEMORY;
@@ -463,26 +528,43 @@ wl_status wl_ns_batch_run(const wl_ns_request* reqs, int count, void* workspace,
     Carver c;
     c.base = static_cast<char*>(workspace);
     NsLayout lay;
-    WL_TRY(plan(reqs, count, c, lay, table.data()));
+    // the requests of each kind together, in the caller's order
+    int n[kNsKinds] = {}, start[kNsKinds], at[kNsKinds];
+    for (int r = 0; r < count; ++r) ++n[place[r]];
+    for (int k = 0, sum = 0; k < kNsKinds; sum += n[k++]) start[k] = at[k] = sum;
+    for (int r = 0; r < count; ++r) place[r] = at[place[r]]++;
+    WL_TRY(plan(reqs, count, c, lay, table.data(), place.data()));
     hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
-    const unsigned zero = 0u;
+    const unsigned zero[kNsKinds] = {};
     WL_CHECK_HIP(hipMemcpyAsync(lay.dev_reqs, table.data(), sizeof(NsReq) * size_t(count),
                                 hipMemcpyHostToDevice, s));
-    WL_CHECK_HIP(hipMemcpyAsync(lay.dev_head, &zero, sizeof(zero), hipMemcpyHostToDevice, s));
-    const int grid = std::min(count, ns_compute_units());
-    k_ns_batch<<<grid, kNsThreads, 0, s>>>(lay.dev_reqs, count, lay.dev_head, lay.dev_res);
-    WL_CHECK_HIP(hipGetLastError());
+    WL_CHECK_HIP(hipMemcpyAsync(lay.dev_head, zero, sizeof(zero), hipMemcpyHostToDevice, s));
+    for (int k = 0; k < kNsKinds; ++k) {
+        if (n[k] == 0) continue;
+        const int grid = std::min(n[k], ns_compute_units());
+        const NsReq* q = lay.dev_reqs + start[k];
+        NsRes* out = lay.dev_res + start[k];
+        unsigned* head = lay.dev_head + k;
+        if (k == kNsRes2)
+            k_ns_batch<kNsRes2><<<grid, kNsThreads, 0, s>>>(q, n[k], head, out);
+        else if (k == kNsRes3)
+            k_ns_batch<kNsRes3><<<grid, kNsThreads, 0, s>>>(q, n[k], head, out);
+        else
+            k_ns_batch<kNsGeneral><<<grid, kNsThreads, 0, s>>>(q, n[k], head, out);
+        WL_CHECK_HIP(hipGetLastError());
+    }
     std::vector<NsRes> res(static_cast<size_t>(count));
     WL_CHECK_HIP(hipMemcpyAsync(res.data(), lay.dev_res, sizeof(NsRes) * size_t(count),
                                 hipMemcpyDeviceToHost, s));
     WL_CHECK_HIP(hipStreamSynchronize(s));
     wl_status worst = WL_OK;
     for (int r = 0; r < count; ++r) {
-        results[r].status = res[r].status;
-        results[r].vcycles = res[r].vcycles;
-        results[r].t = res[r].t;
-        results[r].dt = res[r].dt;
-        if (res[r].status != WL_OK && worst == WL_OK) worst = wl_status(res[r].status);
+        const NsRes& o = res[place[r]];
+        results[r].status = o.status;
+        results[r].vcycles = o.vcycles;
+        results[r].t = o.t;
+        results[r].dt = o.dt;
+        if (o.status != WL_OK && worst == WL_OK) worst = wl_status(o.status);
     }
     if (worst == WL_ERR_NOT_CONVERGED) set_error("some pressure solves reached max_vcycles");
     if (worst == WL_ERR_NONFINITE) set_error("non-finite residual in a batched run");

@@ -78,11 +78,11 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 // WAVE: called by the first wave alone; else by every thread of the workgroup
 // (at least 64 nw), the waves beyond nw only meeting the barriers.
 template <typename T, int PER, bool WAVE>
-__device__ void coarse_cg(const Grid& g, const T* L0, const T* L1, const T* L2, T Lc, int uniform,
+__device__ __forceinline__ void coarse_cg(const Grid& g, const T* L0, const T* L1, const T* L2, T Lc, int uniform,
                            const T* b, T* xout, double tol, int maxit, CgLds& S) {
 #pragma clang fp contract(off)
     const int N = int(cells(g));
-    const int t = int(threadIdx.x);
+    const int t = opaque(int(threadIdx.x));
     const int stride = WAVE ? 64 : 64 * ((N + 64 * PER - 1) / (64 * PER));
     const bool worker = WAVE || t < stride;
     double* su = S.u;

@@ -31,6 +31,15 @@ __device__ __forceinline__ size_t cid(const Grid& g, int i, int j, int k) {
     return size_t(i) + size_t(g.n0) * (size_t(j) + size_t(g.n1) * size_t(k));
 }
 
+// The value, as one the compiler knows nothing about: keeps what is formed from
+// it (addresses, neighbour slots) inside the pass that uses it.  A workgroup
+// that solves in a loop runs the same passes over and over, and the hoisted
+// addresses of all of them took the registers that hold its iterates.
+__device__ __forceinline__ int opaque(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 // Lower / upper neighbour coordinate along one direction (clamped when the
 // direction is not periodic; the face coefficient is zero there).
 __device__ __forceinline__ int nb_lo(int c, int n, int per) {

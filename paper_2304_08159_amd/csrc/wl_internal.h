@@ -220,6 +220,10 @@ struct Hierarchy {
     int* cinv_ok = nullptr;
     bool direct_coarse = true;
     bool cinv_set = false;  // host: the flag has been set since the carve
+    // V-cycle tail (non-uniform levels): w / D of its levels and their class
+    // words, formed when the coefficients change
+    T* tail_wd = nullptr;
+    unsigned* tail_cls = nullptr;
     double* cgpart = nullptr;    // CG per-block partial sums (5 per block of level 0)
     GraphCache graphs;
 };

@@ -225,7 +225,7 @@ void carve_hierarchy(Carver& c, Hierarchy<T>& h, int ndim, const int n[3], const
         h.tail_cls = c.take<unsigned>(size_t(kTailGlobalLevels) * kResThreads);
     }
     const size_t Nc = cells(h.lev[nlev - 1].g);
-    if (Nc <= size_t(kDirectMax)) {
+    if (Nc <= size_t(sizeof(T) == 8 ? kDirectMax64 : kDirectMax)) {
         h.cinv = c.take<double>(Nc * Nc);
         h.cinv_ok = c.take<int>(1);
     }
@@ -1354,26 +1354,87 @@ __device__ void coarse_direct_wave(const Grid& g, const T* L0, const T* L1, cons
         if (own[m]) xout[lane + 64 * m] = act[m] ? T(x[m] - xm) : T(0);
 }
 
+// FP64 coarsest levels of 65 to kDirectMax64 cells: row j of G is the
+// minimum-norm solution for the unit right-hand side e_j, all rows at once, one
+// workgroup each, by the iteration itself run to a residual of 1e-13; a row
+// that does not get there (disconnected active cells) clears *ok and the
+// iteration solves instead.  385 cells past a sphere: formed in 0.1 ms, and a
+// solve is one product (coarse_direct_wg) instead of about a hundred dependent
+// iterations (62 us).  FP32 levels keep the iteration: what its tolerance leaves
+// in the weak modes of nearly closed cells is part of their results.
+__global__ __launch_bounds__(64 * kCgGroupWaves) void k_coarse_columns(Grid g, Coeffs<double> C,
+                                                                       int uniform,
+                                                                       double* __restrict__ G,
+                                                                       int* __restrict__ ok) {
+    __shared__ CgLds S;
+    __shared__ double e[kDirectMax64];
+    const int N = int(cells(g)), j = int(blockIdx.x);
+    for (int c = int(threadIdx.x); c < N; c += int(blockDim.x)) e[c] = c == j ? 1.0 : 0.0;
+    __syncthreads();
+    const bool done = coarse_cg<double, 2, false>(g, C.L0, C.L1, C.L2, C.Lc, uniform, e,
+                                                  G + size_t(j) * N, 1e-13, 2 * N + 64, S);
+    if (!done && threadIdx.x == 0) *ok = 0;
+}
+
+// x = b G by every thread of a workgroup of kResThreads: lane i of part p sums
+// its share of the rows j (coalesced over i, 16 rows in flight), then the parts
+// in order.  One compute unit's share of the L2 rate bounds it: 1.2 MB at 385
+// cells.
+template <typename T>
+__device__ __forceinline__ void coarse_direct_wg(int N, const T* b, T* xout, const double* G,
+                                                 CgLds& S) {
+    const int ni = (N + 63) & ~63, parts = kResThreads / ni;
+    const int t = opaque(int(threadIdx.x)), part = t / ni, i = t - part * ni;
+    for (int c = t; c < N; c += kResThreads) S.u[c] = double(b[c]);
+    __syncthreads();
+    const int per = (N + parts - 1) / parts, j0 = part * per, j1 = min(N, j0 + per);
+    double v = 0.0;
+    if (part < parts && i < N) {
+        const double* __restrict__ col = G + i;
+        int j = j0;
+        for (; j + 16 <= j1; j += 16) {
+            double gv[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) gv[q] = col[size_t(j + q) * N];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) v = fma(gv[q], S.u[j + q], v);
+        }
+        for (; j < j1; ++j) v = fma(col[size_t(j) * N], S.u[j], v);
+    }
+    __syncthreads();
+    if (part > 0 && part < parts && i < N) S.u[part * ni + i] = v;
+    __syncthreads();
+    if (part == 0 && i < N) {
+        for (int q = 1; q < parts; ++q) v = v + S.u[q * ni + i];
+        xout[i] = T(v);
+    }
+}
+
 // The coarsest solve (every thread of the workgroup, or the first wave of one
-// on levels of at most kCgWaveMax cells): the inverse where it is valid, else
-// the iteration.  No barrier at the end.
+// on levels of at most kCgWaveMax cells without an inverse): the inverse where
+// it is valid, else the iteration.  No barrier at the end.
 template <typename T>
 __device__ __forceinline__ void coarse_solve_wg(const Grid& g, const T* L0, const T* L1,
                                                 const T* L2, T Lc, int uniform, const T* b,
                                                 T* xout, double tol, int maxit, const double* G,
                                                 const int* ok, CgLds& S) {
-    if (G && int(cells(g)) <= 64 && *ok) {
-        if (threadIdx.x < 64)
+    const int N = int(cells(g));
+    if (G && *ok) {
+        if (sizeof(T) == 8 && N > kDirectMax)
+            coarse_direct_wg<T>(N, b, xout, G, S);
+        else if (threadIdx.x < 64)
             coarse_direct_wave<T, 1>(g, L0, L1, L2, Lc, uniform, b, xout, G, S.u);
         return;
     }
     coarse_cg_wg<T>(g, L0, L1, L2, Lc, uniform, b, xout, tol, maxit, S);
 }
 
-// The coarsest solve in a launch of its own: one wave, or 64 kCgGroupWaves
-// threads on levels of more than kCgWaveMax cells.
+// The coarsest solve in a launch of its own: kResThreads for the product with an
+// inverse of more than kDirectMax cells; for the iteration one wave, or 64
+// kCgGroupWaves threads (sixteen waves would only add to its barriers: 990
+// cells in FP64, 44 x 36 x 40 steps 19.6 instead of 16.6 ms).
 template <typename T>
-__global__ __launch_bounds__(64 * kCgGroupWaves) void k_coarse_solve(
+__global__ __launch_bounds__(kResThreads) void k_coarse_solve(
     Grid g, Coeffs<T> C, int uniform, const T* __restrict__ b, T* __restrict__ xout, double tol,
     int maxit, const double* G, const int* ok) {
     __shared__ CgLds S;
@@ -1997,7 +2058,9 @@ static wl_status coarse_solve(const Hierarchy<T>& h, const Level<T>& L, T* xout,
         return WL_ERR_INVALID_ARG;
     }
     const bool dir = h.cinv_set && &L == &h.lev[h.nlev - 1];
-    k_coarse_solve<T><<<1, N <= kCgWaveMax ? 64 : 64 * kCgGroupWaves, 0, s>>>(
+    const bool product = dir && h.cinv && N > kDirectMax;
+    const unsigned nt = product ? kResThreads : N <= kCgWaveMax ? 64 : 64 * kCgGroupWaves;
+    k_coarse_solve<T><<<1, nt, 0, s>>>(
         L.g, coeffs_of(L), L.uniform, L.b, xout, h.coarse_tol, maxit, dir ? h.cinv : nullptr,
         dir ? h.cinv_ok : nullptr);
     WL_CHECK_LAUNCH();
@@ -2131,7 +2194,16 @@ wl_status mg_coarsen_all(Hierarchy<T>& h, hipStream_t s) {
     // and keeps the solve (a cleared flag)
     if (h.cinv) {
         const Level<T>& Cst = h.lev[h.nlev - 1];
-        if (h.direct_coarse && !Cst.uniform && direct_coarse_enabled()) {
+        const size_t N = cells(Cst.g);
+        const bool direct = h.direct_coarse && direct_coarse_enabled();
+        if (direct && N > size_t(kDirectMax)) {
+            if constexpr (sizeof(T) == 8) {
+                k_fill<int><<<1, 64, 0, s>>>(h.cinv_ok, 1, 1);
+                WL_CHECK_LAUNCH();
+                k_coarse_columns<<<unsigned(N), unsigned(64 * ((N + 127) / 128)), 0, s>>>(
+                    Cst.g, coeffs_of(Cst), Cst.uniform, h.cinv, h.cinv_ok);
+            }
+        } else if (direct && !Cst.uniform) {
             k_coarse_inverse<T><<<1, 1024, 0, s>>>(Cst.g, coeffs_of(Cst), Cst.uniform, h.cinv,
                                                    h.cinv_ok);
         } else {

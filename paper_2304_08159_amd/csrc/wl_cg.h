@@ -77,9 +77,11 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 
 // WAVE: called by the first wave alone; else by every thread of the workgroup
 // (at least 64 nw), the waves beyond nw only meeting the barriers.
+// Returns whether the residual reached the tolerance.
 template <typename T, int PER, bool WAVE>
-__device__ __forceinline__ void coarse_cg(const Grid& g, const T* L0, const T* L1, const T* L2, T Lc, int uniform,
-                           const T* b, T* xout, double tol, int maxit, CgLds& S) {
+__device__ __forceinline__ bool coarse_cg(const Grid& g, const T* L0, const T* L1, const T* L2,
+                                          T Lc, int uniform, const T* b, T* xout, double tol,
+                                          int maxit, CgLds& S) {
 #pragma clang fp contract(off)
     const int N = int(cells(g));
     const int t = opaque(int(threadIdx.x));
@@ -176,6 +178,7 @@ __device__ __forceinline__ void coarse_cg(const Grid& g, const T* L0, const T* L
     }
     publish();
     double goal = 0.0, inv_rr0 = 0.0, pq = 0.0;
+    bool done = false;
     for (int it = 0; it <= maxit; ++it) {
         double rr = 0.0, rw = 0.0;
 #pragma unroll
@@ -192,7 +195,8 @@ __device__ __forceinline__ void coarse_cg(const Grid& g, const T* L0, const T* L
         }
         sums(rr, rw);
         // converged (or zero from the start), or out of iterations
-        if (!(rr > goal) || it == maxit) break;
+        done = !(rr > goal);
+        if (done || it == maxit) break;
         if (it == 0) goal = tol * tol * rr;
         const double beta = rr * inv_rr0;            // 0 at first
         pq = fma(-beta * beta, pq, rw);              // p M p = r w - beta^2 (p M p before)
@@ -219,6 +223,7 @@ __device__ __forceinline__ void coarse_cg(const Grid& g, const T* L0, const T* L
 #pragma unroll
     for (int m = 0; m < PER; ++m)
         if (own[m]) xout[t + stride * m] = act[m] ? T(x[m] - xm) : T(0);
+    return done;
 }
 
 // The iterative coarsest solve of a workgroup of at least 512 threads (every

@@ -17,6 +17,7 @@ constexpr int kMaxLevels = 16;
 constexpr int kBlock = 256;           // threads per block of the stencil kernels
 constexpr int kCoarseMax = 1024;      // cells a one-workgroup coarsest solve accepts
 constexpr int kDirectMax = 64;        // cells a coarsest level solved by its inverse may have
+constexpr int kDirectMax64 = 512;     // the same on FP64 levels (2 MB, half an XCD's L2)
 
 // ---------------------------------------------------------------- errors
 void set_error(const std::string& msg);
@@ -212,7 +213,8 @@ struct Hierarchy {
     size_t n_active = 0;         // active fine cells (host copy)
     int pairs = 0;               // fused two-sweep kernels: 0 off, 1 on large levels, 2 on all
     int smoother = 0;            // 0 damped Jacobi, 1 conjugate gradients (WL_SMOOTH_*)
-    // coarsest levels of at most kDirectMax cells: the inverse of the
+    // coarsest levels of at most kDirectMax cells (kDirectMax64 in FP64, see
+    // k_coarse_columns): the inverse of the
     // operator with the mean constraint (N x N, FP64; see k_coarse_inverse)
     // and its validity flag, formed when the coefficients change unless
     // direct_coarse is off (then the CG solves)

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 GRIDS = [((5, 3), (False, False)), ((8, 8), (True, True)), ((13, 5), (False, True)),
          ((16, 8), (False, False)), ((43, 3), (False, False)), ((11, 7, 5), (False, False, False)),
          ((9, 7, 11), (True, True, True)), ((16, 8, 8), (False, True, False)),
-         ((32, 32), (False, False))]
+         ((32, 16), (False, False)), ((27, 19), (True, False)), ((32, 32), (False, False))]
 
 
 def _dense(n, per, L):
@@ -49,10 +49,14 @@ def _dev(a, n, dtype):
     return torch.from_numpy(a.reshape(shape).copy()).to(dtype).cuda().contiguous()
 
 
-@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("prec", ["fp64", "fp64-cg", "fp32"])
 @pytest.mark.parametrize("n,per", GRIDS, ids=["x".join(map(str, g[0])) for g in GRIDS])
-def test_one_level_solve_is_the_minimum_norm_solution(n, per, prec):
+def test_one_level_solve_is_the_minimum_norm_solution(n, per, prec, monkeypatch):
+    """fp64 takes the level's inverse up to 512 cells, fp64-cg the iteration."""
     import paper_2304_08159_amd as wl
+    if prec == "fp64-cg":
+        monkeypatch.setenv("WL_DIRECT_COARSE", "0")
+        prec = "fp64"
     dtype = torch.float64 if prec == "fp64" else torch.float32
     L, b = _problem(n, per, 3)
     M = _dense(n, per, L)

@@ -74,12 +74,26 @@ __device__ bool face_adj(const VelField<T>& E, T* const* Rb, int c, int d, int i
     if (Fb == T(0)) return false;
     const int di = d == 0, dj = d == 1, dk = d == 2;
     const int ci = c == 0, cj = c == 1, ck = c == 2;
-    const T um2 = vget<T, ALLPER>(E, c, i - 2 * di, j - 2 * dj, k - 2 * dk);
-    const T um1 = vget<T, ALLPER>(E, c, i - di, j - dj, k - dk);
-    const T u0 = vget<T, ALLPER>(E, c, i, j, k);
-    const T up1 = vget<T, ALLPER>(E, c, i + di, j + dj, k + dk);
-    const T ubar = T(0.5) * (vget<T, ALLPER>(E, d, i, j, k) +
-                             vget<T, ALLPER>(E, d, i - ci, j - cj, k - ck));
+    T um2, um1, u0, up1, a0, a1;
+    if (!ALLPER && flux_inside(E, c, d, i, j, k)) {
+        const size_t at = cid(g, i, j, k);
+        const ptrdiff_t st = di + ptrdiff_t(g.n0) * (dj + ptrdiff_t(g.n1) * dk);
+        const T *uc = E.u[c] + at, *ud = E.u[d] + at;
+        um2 = uc[-2 * st];
+        um1 = uc[-st];
+        u0 = uc[0];
+        up1 = uc[st];
+        a0 = ud[0];
+        a1 = ud[-(ci + ptrdiff_t(g.n0) * (cj + ptrdiff_t(g.n1) * ck))];
+    } else {
+        um2 = vget_flat<T, ALLPER>(E, c, i - 2 * di, j - 2 * dj, k - 2 * dk);
+        um1 = vget_flat<T, ALLPER>(E, c, i - di, j - dj, k - dk);
+        u0 = vget_flat<T, ALLPER>(E, c, i, j, k);
+        up1 = vget_flat<T, ALLPER>(E, c, i + di, j + dj, k + dk);
+        a0 = vget_flat<T, ALLPER>(E, d, i, j, k);
+        a1 = vget_flat<T, ALLPER>(E, d, i - ci, j - cj, k - ck);
+    }
+    const T ubar = T(0.5) * (a0 + a1);
     const bool pos = ubar >= T(0);
     const T cu = pos ? um1 : u0;
     const T bd = pos ? u0 : um1;
@@ -138,7 +152,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_flux(TileDev TL, VelField<T> E, 
     const int i = sp.i - 2, j = sp.j - 2;
     for (int kk = sp.z0; kk < sp.z1; ++kk) {
         const int k = kk - pg.o2;
-        for (int c = 0; c < g.ndim; ++c) {
+        for (int c = int(blockIdx.y); c < g.ndim; c += int(gridDim.y)) {
             T acc = T(0);
             T w[4], wphi;
             for (int d = 0; d < g.ndim; ++d) {
@@ -172,7 +186,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_bdim(TileDev TL, Grid g, AdjPtrs
     const int i = sp.i - 2, j = sp.j - 2;
     for (int kk = sp.z0; kk < sp.z1; ++kk) {
         const int k = kk - pg.o2;
-        for (int c = 0; c < g.ndim; ++c) {
+        for (int c = int(blockIdx.y); c < g.ndim; c += int(gridDim.y)) {
             T acc = T(0);
             if (in_grid(g, i, j, k) && interior(g, c, i, j, k)) {
                 const size_t id = cid(g, i, j, k);
@@ -286,7 +300,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_fold(TileDev TL, VelField<T> G, 
     if (i >= g.n0 || j >= g.n1) return;
     for (int k = sp.z0; k < sp.z1; ++k) {
         const int K[3] = {i, j, k};
-        for (int c = 0; c < g.ndim; ++c) {
+        for (int c = int(blockIdx.y); c < g.ndim; c += int(gridDim.y)) {
             if (!interior(g, c, i, j, k)) continue;
             const T* P = pad.a[c];
             Pre pr[3];
@@ -309,7 +323,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_fold(TileDev TL, VelField<T> G, 
                     }
             acc.p[c][cid(g, i, j, k)] += v;
         }
-        if (accout && G.bchi[0] == WL_BC_OUTFLOW && i == g.n0 - 1) {
+        if (blockIdx.y == 0 && accout && G.bchi[0] == WL_BC_OUTFLOW && i == g.n0 - 1) {
             // the outflow plane: x ghosts n0, n0+1 of component 0, times the
             // tangential preimages of (j, k)
             const T* P = pad.a[0];
@@ -684,9 +698,9 @@ wl_status adj_flux(const VelField<T>& E, T* const Rbar[3], T nu, const PadField<
     const Launch ln = launch_for(out.pg.P0, out.pg.P1, out.pg.P2);
     AdjPtrs<T> R{{Rbar[0], Rbar[1], Rbar[2]}};
     if (allper)
-        k_adj_flux<T, true><<<ln.grid, ln.block, 0, s>>>(ln.td, E, R, nu, out);
+        k_adj_flux<T, true><<<split_components(ln, E.g), ln.block, 0, s>>>(ln.td, E, R, nu, out);
     else
-        k_adj_flux<T, false><<<ln.grid, ln.block, 0, s>>>(ln.td, E, R, nu, out);
+        k_adj_flux<T, false><<<split_components(ln, E.g), ln.block, 0, s>>>(ln.td, E, R, nu, out);
     WL_CHECK_LAUNCH();
     return WL_OK;
 }
@@ -698,7 +712,7 @@ wl_status adj_bdim(const Grid& g, T* const gbar[3], T* const mu0[3], T* const mu
     AdjPtrs<T> gb{{gbar[0], gbar[1], gbar[2]}}, m0{{mu0[0], mu0[1], mu0[2]}};
     AdjPtrs9<T> m1;
     for (int q = 0; q < 9; ++q) m1.p[q] = mu1n[q];
-    k_adj_bdim<T><<<ln.grid, ln.block, 0, s>>>(ln.td, g, gb, m0, m1, out);
+    k_adj_bdim<T><<<split_components(ln, g), ln.block, 0, s>>>(ln.td, g, gb, m0, m1, out);
     WL_CHECK_LAUNCH();
     return WL_OK;
 }
@@ -720,7 +734,7 @@ wl_status adj_fold(const VelField<T>& geom, const PadField<T>& pad, T* const acc
                    hipStream_t s) {
     const Launch ln = launch_for(geom.g.n0, geom.g.n1, geom.g.n2);
     AdjPtrs<T> a{{acc[0], acc[1], acc[2]}};
-    k_adj_fold<T><<<ln.grid, ln.block, 0, s>>>(ln.td, geom, pad, a, acc_out);
+    k_adj_fold<T><<<split_components(ln, geom.g), ln.block, 0, s>>>(ln.td, geom, pad, a, acc_out);
     WL_CHECK_LAUNCH();
     return WL_OK;
 }

@@ -196,6 +196,8 @@ struct SimImpl {
     T* mu1n[9];
     unsigned char* tile_cls = nullptr;  // BDIM tile classes (one per block of the cell tiling)
     unsigned char* cell_flag = nullptr;  // BDIM per-cell flags (bodies only)
+    unsigned* cell_list = nullptr;       // the flagged cells and their number (bodies at rest)
+    unsigned ncell = 0;
     Hierarchy<T> h;
     Reduce red;
     double* scal = nullptr;  // [0] dt, [1] dt_next, [2] cfl max
@@ -232,6 +234,7 @@ static void carve_sim(Carver& c, SimImpl<T>& s, const SimConfig& cfg) {
     for (int i = 0; i < 9; ++i) s.mu1n[i] = c.take<T>(N);
     s.tile_cls = c.take<unsigned char>(reduce_slots_for(cfg.g));
     s.cell_flag = cfg.body ? c.take<unsigned char>(N) : nullptr;
+    s.cell_list = cfg.body && !cfg.moving && N < (size_t(1) << 32) ? c.take<unsigned>(N + 1) : nullptr;
     const int per[3] = {cfg.g.per0, cfg.g.per1, cfg.g.per2};
     carve_hierarchy<T>(c, s.h, cfg.d.ndim, cfg.d.n, per, cfg.nlev, cfg.d.prec == WL_MIXED);
     // a body that moves re-measures every step: the coarsest inverse would be
@@ -339,6 +342,8 @@ static BdimFields<T> bdim_fields(const SimImpl<T>& s) {
     for (int i = 0; i < 9; ++i) b.mu1n[i] = s.mu1n[i];
     b.cls = s.tile_cls;
     b.cflag = s.cell_flag;
+    b.clist = s.cell_list;
+    b.ncell = s.ncell;
     return b;
 }
 
@@ -358,6 +363,7 @@ static wl_status sim_measure(SimImpl<T>& s, double t, hipStream_t st) {
     for (int i = 0; i < 9; ++i) M.mu1n[i] = s.mu1n[i];
     WL_TRY(ns_measure<T>(c.g, body, c.d.bc_lo, M, st));
     if (c.body) WL_TRY(ns_tile_class<T>(c.g, bdim_fields(s), s.tile_cls, st, s.cell_flag));
+    if (s.cell_list) WL_TRY(ns_flag_list(c.g, s.cell_flag, s.cell_list, &s.ncell, st));
     s.h.lev[0].uniform = c.unif ? 1 : 0;
     s.h.lev[0].Lc = T(1);
     WL_TRY(mg_coarsen_all<T>(s.h, st));

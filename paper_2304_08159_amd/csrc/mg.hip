@@ -1790,6 +1790,7 @@ wl_status fill(T* p, size_t n, T v, hipStream_t s) {
 }
 template wl_status fill<float>(float*, size_t, float, hipStream_t);
 template wl_status fill<double>(double*, size_t, double, hipStream_t);
+template wl_status fill<unsigned>(unsigned*, size_t, unsigned, hipStream_t);
 
 template <typename Tin, typename Tout>
 __global__ void k_convert(const Tin* __restrict__ a, Tout* __restrict__ b, size_t n) {

@@ -28,6 +28,10 @@ struct BdimFields {
     // Per cell: 1 where the blend differs from f on any face of the cell
     // (mu0 != 1 or a nonzero mu1 n component); null: every cell.
     const unsigned char* cflag = nullptr;
+    // The flagged cells' indices (bodies at rest), and their number; null: look
+    // at every flag.
+    const unsigned* clist = nullptr;
+    unsigned ncell = 0;
 };
 
 template <typename T>
@@ -109,6 +113,10 @@ wl_status ns_bdim_in_place(const VelField<T>& F, T* const f[3], const BdimFields
 template <typename T>
 wl_status ns_tile_class(const Grid& g, const BdimFields<T>& B, unsigned char* cls, hipStream_t s,
                         unsigned char* cflag = nullptr);
+// The indices of the flagged cells into list (unordered) and their number into
+// list[cells(g)], which is also copied to *count on the host (synchronises).
+wl_status ns_flag_list(const Grid& g, const unsigned char* cflag, unsigned* list, unsigned* count,
+                       hipStream_t s);
 // p_check (periodic, uniform, 3D): also the first residual check of the
 // pressure solve that starts from p, with Poisson coefficient Lp (partials of
 // [sigma, sigma^2, c, c^2], c = sigma - A p; see k_divergence).

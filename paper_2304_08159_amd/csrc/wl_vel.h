@@ -67,6 +67,64 @@ __device__ __forceinline__ T vget(const VelField<T>& V, int c, int i, int j, int
     return V.u[c][cid(g, q[0], q[1], q[2])];
 }
 
+// vget without branches: one load from the address the rule picks, then a sign
+// or a constant.  For the adjoint's gather, which makes 324 of these per cell
+// and with the rule as branches waited for the load of each (64 x 32 x 32 in
+// FP64: 314 -> 189 us with the loads of a face in flight together); the forward
+// kernels make a tenth of that, where the selects cost more than the branches
+// (momentum there 36 -> 49 us).
+template <typename T, bool ALLPER>
+__device__ __forceinline__ T vget_flat(const VelField<T>& V, int c, int i, int j, int k) {
+    const Grid& g = V.g;
+    if (ALLPER) return vget<T, true>(V, c, i, j, k);
+    // the grid and boundary fields are uniform; through readfirstlane a choice
+    // between two of them stays a choice between registers
+    auto u_ = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    const int n0 = u_(g.n0), n1 = u_(g.n1), n2 = u_(g.n2);
+    const bool p0 = u_(g.per0), p1 = u_(g.per1), p2 = u_(g.per2);
+    if (p0) i = i < 0 ? i + n0 : (i >= n0 ? i - n0 : i);
+    if (p1) j = j < 0 ? j + n1 : (j >= n1 ? j - n1 : j);
+    if (p2) k = k < 0 ? k + n2 : (k >= n2 ? k - n2 : k);
+    const bool o0 = unsigned(i) >= unsigned(n0), o1 = unsigned(j) >= unsigned(n1);
+    const bool o2 = unsigned(k) >= unsigned(n2), out = o0 || o1 || o2;
+    const int d = o0 ? 0 : (o1 ? 1 : 2);
+    const int kk = o0 ? i : (o1 ? j : k), m = o0 ? n0 : (o1 ? n1 : n2);
+    const bool in0 = u_(V.bclo[0]) == WL_BC_INFLOW, in1 = u_(V.bclo[1]) == WL_BC_INFLOW;
+    const bool in2 = u_(V.bclo[2]) == WL_BC_INFLOW;
+    const bool ex0 = u_(V.bchi[0]) == WL_BC_OUTFLOW, ex1 = u_(V.bchi[1]) == WL_BC_OUTFLOW;
+    const bool ex2 = u_(V.bchi[2]) == WL_BC_OUTFLOW;
+    const bool low = kk < 0, normal = c == d;
+    const bool inflow = o0 ? in0 : (o1 ? in1 : in2), exits = o0 ? ex0 : (o1 ? ex1 : ex2);
+    // the cell along d: mirrored below, the last one or the one before above
+    const int mir = normal ? -kk : -1 - kk;
+    int idx = mir < m ? mir : (normal ? 0 : m - 1);
+    if (!low) idx = normal || exits || kk == m ? m - 1 : m - 2;
+    idx = min(max(idx, 0), m - 1);
+    const int x = o0 ? idx : i, yc = min(max(j, 0), n1 - 1), zc = min(max(k, 0), n2 - 1);
+    const int y = out && d == 1 ? idx : yc, z = out && d == 2 ? idx : zc;
+    const bool plane = out && !low && normal && exits;
+    const T* base = plane ? V.uout : V.u[c];
+    const size_t off = plane ? size_t(yc) + size_t(n1) * size_t(zc)
+                             : size_t(x) + size_t(n0) * (size_t(y) + size_t(n1) * size_t(z));
+    const T v = base[off];
+    const bool above = out && !low && normal && !exits;  // wall: face 0, beyond it odd
+    const T w = (out && low && normal && !inflow) || (above && kk != m) ? -v : v;
+    return out && low && inflow ? V.U[c] : (above && kk == m ? T(0) : w);
+}
+
+// Whether the stencil of a flux through a lower d-face at (i, j, k) (two cells
+// below, one above along d; the advecting pair one below along c) lies inside
+// the grid for every active lane.
+template <typename T>
+__device__ __forceinline__ bool flux_inside(const VelField<T>& V, int c, int d, int i, int j, int k) {
+    const Grid& g = V.g;
+    const int li = max(d == 0 ? 2 : 0, c == 0 ? 1 : 0), lj = max(d == 1 ? 2 : 0, c == 1 ? 1 : 0);
+    const int lk = max(d == 2 ? 2 : 0, c == 2 ? 1 : 0);
+    const bool in = i >= li && i + (d == 0) < g.n0 && j >= lj && j + (d == 1) < g.n1 && k >= lk &&
+                    k + (d == 2) < g.n2;
+    return __all(in);
+}
+
 // Pressure-gradient update of one face: u - cl (p_here - p_lower) with
 // cl = c dt L, one rounding (shared by the projection kernel and the
 // momentum kernel that applies the predictor projection on the fly).

@@ -366,8 +366,10 @@ static wl_status sim_measure(SimImpl<T>& s, double t, hipStream_t st) {
     if (s.cell_list) WL_TRY(ns_flag_list(c.g, s.cell_flag, s.cell_list, &s.ncell, st));
     s.h.lev[0].uniform = c.unif ? 1 : 0;
     s.h.lev[0].Lc = T(1);
+    const bool mixed = c.d.prec == WL_MIXED;
+    WL_TRY(mg_flag_odd<T>(s.h, mixed ? &s.mix : nullptr, st));
+    if (mixed) WL_TRY(mg_mixed_classes(c.g, s.mix, s.h.odd, st));
     WL_TRY(mg_coarsen_all<T>(s.h, st));
-    if (c.d.prec == WL_MIXED) WL_TRY(mg_mixed_classes(c.g, s.mix, st));
     return mg_count_active<T>(s.h, s.red, st);
 }
 
@@ -947,8 +949,7 @@ static wl_status poisson_solve_plain(wl_poisson* ps, const void* coeffs, void* x
     PoissonImpl<T>& P = *static_cast<PoissonImpl<T>*>(ps->impl);
     hipStream_t st = ps->stream;
     if (coeffs) {
-        WL_TRY((mg_load_coeffs<T, T>(P.g, static_cast<const T*>(coeffs), P.h.lev[0].L, nullptr, st)));
-        P.h.lev[0].uniform = 0;
+        WL_TRY((mg_load_coeffs<T, T>(P.h, static_cast<const T*>(coeffs), nullptr, st)));
         WL_TRY(mg_coarsen_all<T>(P.h, st));
         WL_TRY(mg_count_active<T>(P.h, P.red, st));
         P.have = true;
@@ -967,12 +968,10 @@ static wl_status poisson_solve_mixed(wl_poisson* ps, const void* coeffs, void* x
     PoissonMixedImpl& P = *static_cast<PoissonMixedImpl*>(ps->impl);
     hipStream_t st = ps->stream;
     if (coeffs) {
-        WL_TRY((mg_load_coeffs<double, float>(P.g, static_cast<const double*>(coeffs), P.h.lev[0].L,
-                                              P.mix.L, st)));
-        P.h.lev[0].uniform = 0;
+        WL_TRY((mg_load_coeffs<double, float>(P.h, static_cast<const double*>(coeffs), P.mix.L, st)));
+        WL_TRY(mg_mixed_classes(P.g, P.mix, P.h.odd, st));
         WL_TRY(mg_coarsen_all<float>(P.h, st));
-        WL_TRY(mg_mixed_classes(P.g, P.mix, st));
-        WL_TRY(mg_count_active64(P.g, P.mix.L, P.red, &P.h.n_active, st));
+        WL_TRY(mg_count_active64(P.g, P.mix, P.red, &P.h.n_active, st));
         P.have = true;
     }
     if (!P.have) return invalid("no coefficients given yet");

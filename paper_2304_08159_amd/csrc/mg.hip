@@ -216,6 +216,9 @@ void carve_hierarchy(Carver& c, Hierarchy<T>& h, int ndim, const int n[3], const
         const Grid& g0 = h.lev[0].g;
         h.cgpart = c.take<double>(5 * reduce_slots_for(g0));
     }
+    size_t slots = 0;
+    for (int l = 0; l < nlev; ++l) slots = std::max(slots, reduce_slots_for(h.lev[l].g));
+    h.odd = c.take<unsigned char>(slots);
     // w / D and class words of the V-cycle tail's levels
     if (h.pairs && nlev >= 3) {
         size_t nt = 0;
@@ -387,7 +390,7 @@ struct PairTile {
 // MODE 0: a uniform, fully periodic level (wD = w / D).  MODE 1 / 2: a
 // non-uniform level with any boundaries, in two launches over the same
 // workgroups: MODE 1 runs the workgroups whose widened region is of class 0
-// (see k_pair_class; face coefficients from the position), MODE 2 the others
+// (see k_classes; face coefficients from the position), MODE 2 the others
 // (coefficients read), so each instance keeps its own register budget:
 // MODE 1 runs over all workgroups and leaves the class-1 ones at once, MODE 2
 // over the list fpl of the class-1 workgroups (fpl[P.nb] of them), each
@@ -1507,87 +1510,173 @@ __global__ __launch_bounds__(kResThreads) void k_tail_classes(TailArgs<T> A) {
             A.cls[A.lev[l].ocw + int(threadIdx.x)] = res_classify<T, D3, RS_TILED>(A.lev[l], A.omega);
 }
 
-// Per-block class of a level for a tiling (see Coeffs::cls): 0 when every
-// face any cell of the block reads equals Lc, or 0 on a non-periodic
-// domain-boundary face (exact comparisons: class-0 blocks then compute
-// bitwise what reading the arrays gives).
+// ------------------------------------------------ classes of the tilings
+// A workgroup of a tiling has class 0 when every face that its cells read
+// equals Lc, or 0 on a non-periodic domain boundary (exact comparisons: a
+// workgroup of class 0 then computes bitwise what reading the arrays gives).
+// Three tilings of a level are classified (the sweeps', the restriction's and
+// the fused pairs').  Each by itself read all coefficients, with neighbours:
+// 268 us for the pairs' and 65 us (mean over two levels) for each of the other
+// two on 256^3 cells in FP64.  So whatever writes the coefficients also leaves
+// an odd-face flag per workgroup of the launch_for tiling (odd_face: a lower
+// face of its own cells that is neither), and k_classes reads coefficients
+// only where a flag is set near the workgroup.  A solve with new coefficients
+// (one sphere): 8.80 -> 8.29 ms on 256^3 cells in FP64, 9.75 -> 8.84 ms on
+// 384^3 mixed.
+
+// Whether a lower face of a cell is neither Lc nor a closed domain boundary.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_level_class(TileDev TL, Grid g, Coeffs<T> C,
-                                                        unsigned char* __restrict__ cls) {
-    __shared__ int any;
-    if (threadIdx.x == 0) any = 0;
-    __syncthreads();
+__device__ __forceinline__ bool odd_face(const Grid& g, int i, int j, int k, T Lc, T Lx, T Ly, T Lz) {
+    const bool ox = Lx != ((i == 0 && !g.per0) ? T(0) : Lc);
+    const bool oy = Ly != ((j == 0 && !g.per1) ? T(0) : Lc);
+    const bool oz = g.ndim == 3 && Lz != ((k == 0 && !g.per2) ? T(0) : Lc);
+    return ox || oy || oz;
+}
+
+// The workgroup's flag: whether any of its threads saw an odd face.
+__device__ __forceinline__ void store_odd(bool odd, unsigned char* __restrict__ flags) {
+    const int any = __syncthreads_or(odd ? 1 : 0);
+    if (threadIdx.x == 0) flags[block_linear()] = any ? 1 : 0;
+}
+
+// Odd-face flags of coefficients that another kernel has written.
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_odd(TileDev TL, Grid g, Coeffs<T> C,
+                                                unsigned char* __restrict__ flags) {
     const Span sp = tile_span(TL, g.n0, g.n1, g.n2);
     const int i = sp.i, j = sp.j;
     bool odd = false;
     if (i < g.n0 && j < g.n1)
-        for (int k = sp.z0; k < sp.z1 && !odd; ++k) {
+        for (int k = sp.z0; k < sp.z1; ++k) {
             const size_t id = cid(g, i, j, k);
-            T Lxl, Lxu, Lyl, Lyu, Lzl, Lzu;
-            walled_faces<T>(g, i, j, k, C.Lc, Lxl, Lxu, Lyl, Lyu, Lzl, Lzu);
-            odd = odd || C.L0[id] != Lxl || C.L1[id] != Lyl;
-            if (i < g.n0 - 1 || g.per0) odd = odd || C.L0[cid(g, nb_up(i, g.n0, g.per0), j, k)] != Lxu;
-            if (j < g.n1 - 1 || g.per1) odd = odd || C.L1[cid(g, i, nb_up(j, g.n1, g.per1), k)] != Lyu;
-            if (g.ndim == 3) {
-                odd = odd || C.L2[id] != Lzl;
-                if (k < g.n2 - 1 || g.per2)
-                    odd = odd || C.L2[cid(g, i, j, nb_up(k, g.n2, g.per2))] != Lzu;
-            }
+            odd |= odd_face<T>(g, i, j, k, C.Lc, C.L0[id], C.L1[id], g.ndim == 3 ? C.L2[id] : T(0));
         }
-    if (odd) any = 1;  // benign race: every writer stores 1
-    __syncthreads();
-    if (threadIdx.x == 0) cls[block_linear()] = any ? 1 : 0;
+    store_odd(odd, flags);
 }
 
-// Class of each fused-pair workgroup (k_smooth_pair, MODE 1 / 2): 0 when every
-// face of every cell whose first sweep the workgroup computes (its tile
-// widened by one cell in x and y, its z chunk by one plane on either side;
-// cells outside a non-periodic direction excluded) equals what walled_faces
-// gives, else 1.  The workgroup-to-tile map is the pair kernel's.
+// A level's tilings and their classes (nb 0: not classified).
+struct ClassArgs {
+    TileDev flags;            // the odd-face flags' tiling
+    TileDev a, b;             // launch_for, launch_pairs
+    PairTile p;
+    int ptx;                  // cells per fused-pair tile in x
+    unsigned char *ca, *cb, *cp;
+};
+
+// Flag tiles met by the cells lo .. hi of a direction, -1 <= lo and
+// hi <= n + 1, wrapped or clipped at the ends: n from t0 on, then those of
+// the wrapped cells -1, n and n + 1 (-1: none).
+struct AxisTiles {
+    int t0, n, e0, e1, e2;
+    __device__ int at(int q) const { return q < n ? t0 + q : (q == n ? e0 : (q == n + 1 ? e1 : e2)); }
+};
+__device__ __forceinline__ AxisTiles axis_tiles(int lo, int hi, int n, int per, int w) {
+    AxisTiles r;
+    r.e0 = lo < 0 && per ? (lo + n) / w : -1;
+    r.e1 = hi >= n && per ? 0 : -1;
+    r.e2 = hi > n && per ? 1 / w : -1;
+    r.t0 = max(lo, 0) / w;
+    r.n = min(hi, n - 1) / w - r.t0 + 1;
+    return r;
+}
+
+// Classes of all tilings of a level in one launch.  The cells of a fused-pair
+// workgroup are those whose first sweep it computes: its tile widened by one
+// cell in x and y, its z chunk by one plane on either side (cells outside a
+// non-periodic direction excluded).  The workgroup-to-tile maps are those of
+// the kernels that use the classes.
 template <typename T>
-__global__ __launch_bounds__(256) void k_pair_class(PairTile P, Grid g, int tx, Coeffs<T> C,
-                                                    unsigned char* __restrict__ cls) {
-    __shared__ int any;
-    if (threadIdx.x == 0) any = 0;
-    __syncthreads();
+__global__ __launch_bounds__(kBlock) void k_classes(ClassArgs A, Grid g, Coeffs<T> C,
+                                                    const unsigned char* __restrict__ flags) {
     unsigned blk = blockIdx.x;
-    if (P.remap) blk = (blk & 7u) * (P.nb >> 3) + (blk >> 3);
-    const int tix = int(blk % unsigned(P.tx));
-    blk /= unsigned(P.tx);
-    const int tiy = int(blk % unsigned(P.ty));
-    const int z0 = int(blk / unsigned(P.ty)) * P.zc;
-    const int z1 = min(z0 + P.zc, g.n2);
-    const int i0 = tix * tx, j0 = tiy * kPairTY;
-    const int wx = tx + 2, wy = kPairTY + 2, wz = z1 - z0 + 2;
-    const int count = wx * wy * wz;
-    bool odd = false;
-    for (int q = int(threadIdx.x); q < count && !odd; q += int(blockDim.x)) {
-        int i = i0 - 1 + q % wx;
-        int j = j0 - 1 + (q / wx) % wy;
-        int k = z0 - 1 + q / (wx * wy);
-        if (i < 0 || i >= g.n0) {
-            if (!g.per0) continue;
-            i = i < 0 ? i + g.n0 : i - g.n0;
-        }
-        if (j < 0 || j >= g.n1) {
-            if (!g.per1) continue;
-            j = j < 0 ? j + g.n1 : j - g.n1;
-        }
-        if (k < 0 || k >= g.n2) {
-            if (!g.per2) continue;
-            k = k < 0 ? k + g.n2 : k - g.n2;
-        }
-        const size_t id = cid(g, i, j, k);
-        T Lxl, Lxu, Lyl, Lyu, Lzl, Lzu;
-        walled_faces<T>(g, i, j, k, C.Lc, Lxl, Lxu, Lyl, Lyu, Lzl, Lzu);
-        odd = odd || C.L0[id] != Lxl || C.L1[id] != Lyl || C.L2[id] != Lzl;
-        if (i < g.n0 - 1 || g.per0) odd = odd || C.L0[cid(g, nb_up(i, g.n0, g.per0), j, k)] != Lxu;
-        if (j < g.n1 - 1 || g.per1) odd = odd || C.L1[cid(g, i, nb_up(j, g.n1, g.per1), k)] != Lyu;
-        if (k < g.n2 - 1 || g.per2) odd = odd || C.L2[cid(g, i, j, nb_up(k, g.n2, g.per2))] != Lzu;
+    unsigned char* cls;
+    int i0, i1, j0, j1, k0, k1;  // cells [i0, i1) x [j0, j1) x [k0, k1)
+    if (blk < A.a.nb + A.b.nb) {
+        const bool first = blk < A.a.nb;
+        const TileDev& TL = first ? A.a : A.b;
+        if (!first) blk -= A.a.nb;
+        cls = (first ? A.ca : A.cb) + blk;
+        unsigned t = blk;
+        if (TL.remap) t = (t & 7u) * (TL.nb >> 3) + (t >> 3);
+        const int bx = 1 << TL.lbx, by = kBlock >> TL.lbx;
+        i0 = int(t % unsigned(TL.tx)) * bx;
+        t /= unsigned(TL.tx);
+        j0 = int(t % unsigned(TL.ty)) * by;
+        k0 = int(t / unsigned(TL.ty)) * TL.zc;
+        i1 = min(i0 + bx, g.n0);
+        j1 = min(j0 + by, g.n1);
+        k1 = min(k0 + TL.zc, g.n2);
+    } else {
+        blk -= A.a.nb + A.b.nb;
+        cls = A.cp + blk;
+        unsigned t = blk;
+        if (A.p.remap) t = (t & 7u) * (A.p.nb >> 3) + (t >> 3);
+        i0 = int(t % unsigned(A.p.tx)) * A.ptx - 1;
+        t /= unsigned(A.p.tx);
+        j0 = int(t % unsigned(A.p.ty)) * kPairTY - 1;
+        k0 = int(t / unsigned(A.p.ty)) * A.p.zc - 1;
+        i1 = i0 + A.ptx + 2;
+        j1 = j0 + kPairTY + 2;
+        k1 = min(k0 + 1 + A.p.zc, g.n2) + 1;
     }
-    if (odd) any = 1;  // benign race: every writer stores 1
-    __syncthreads();
-    if (threadIdx.x == 0) cls[blockIdx.x] = any ? 1 : 0;
+    // the faces read are the lower ones of these cells and of those at i1, j1
+    // and k1 (there only the face of that direction)
+    const AxisTiles X = axis_tiles(i0, i1, g.n0, g.per0, 1 << A.flags.lbx);
+    const AxisTiles Y = axis_tiles(j0, j1, g.n1, g.per1, kBlock >> A.flags.lbx);
+    const AxisTiles Z = axis_tiles(k0, k1, g.n2, g.per2, A.flags.zc);
+    const int cx = X.n + 3, cy = Y.n + 3, cz = Z.n + 3;
+    bool odd = false;
+    for (int q = int(threadIdx.x); q < cx * cy * cz; q += kBlock) {
+        const int tx = X.at(q % cx), ty = Y.at(q / cx % cy), tz = Z.at(q / (cx * cy));
+        if (tx < 0 || ty < 0 || tz < 0) continue;
+        unsigned t = unsigned(tx) + unsigned(A.flags.tx) * (unsigned(ty) + unsigned(A.flags.ty) * unsigned(tz));
+        if (A.flags.remap) t = t % (A.flags.nb >> 3) * 8u + t / (A.flags.nb >> 3);
+        odd |= flags[t] != 0;
+    }
+    if (__syncthreads_or(odd ? 1 : 0)) {
+        odd = false;
+        const bool d3 = g.ndim == 3;
+        const int wx = i1 - i0 + 1, wy = j1 - j0 + 1, wz = d3 ? k1 - k0 + 1 : 1;
+        // cells q, q + kBlock, ... in the order x, y, z: the step as offsets
+        const int sx = kBlock % wx, sy = kBlock / wx % wy, sz = kBlock / (wx * wy);
+        int di = int(threadIdx.x) % wx, dj = int(threadIdx.x) / wx % wy, dk = int(threadIdx.x) / (wx * wy);
+        while (dk < wz && !odd) {
+            int i = i0 + di, j = j0 + dj, k = k0 + dk;
+            const bool ex = i == i1, ey = j == j1, ez = d3 && k == k1;
+            bool out = false;
+            if (i < 0 || i >= g.n0) {
+                out = !g.per0;
+                i = i < 0 ? i + g.n0 : i - g.n0;
+            }
+            if (j < 0 || j >= g.n1) {
+                out = out || !g.per1;
+                j = j < 0 ? j + g.n1 : j - g.n1;
+            }
+            if (d3 && (k < 0 || k >= g.n2)) {
+                out = out || !g.per2;
+                k = k < 0 ? k + g.n2 : k - g.n2;
+            }
+            if (!out) {
+                const size_t id = cid(g, i, j, k);
+                if (!ey && !ez) odd = odd || C.L0[id] != ((i == 0 && !g.per0) ? T(0) : C.Lc);
+                if (!ex && !ez) odd = odd || C.L1[id] != ((j == 0 && !g.per1) ? T(0) : C.Lc);
+                if (d3 && !ex && !ey) odd = odd || C.L2[id] != ((k == 0 && !g.per2) ? T(0) : C.Lc);
+            }
+            di += sx;
+            dj += sy;
+            dk += sz;
+            if (di >= wx) {
+                di -= wx;
+                ++dj;
+            }
+            if (dj >= wy) {
+                dj -= wy;
+                ++dk;
+            }
+        }
+        odd = __syncthreads_or(odd ? 1 : 0) != 0;
+    }
+    if (threadIdx.x == 0) *cls = odd ? 1 : 0;
 }
 
 // Ordered list of the class-1 workgroups of a fused-pair tiling: list[k] the
@@ -1614,31 +1703,39 @@ __global__ __launch_bounds__(1024) void k_pair_list(const unsigned char* __restr
     if (t == 1023u) list[nb] = part[1023];
 }
 
-// Coarse coefficient = 1/2 * sum of the fine faces the coarse face covers.
+// Coarse coefficient = 1/2 * sum of the fine faces the coarse face covers;
+// flags (null: none): the odd-face flags of the coarse level.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_coarsen(TileDev TL, Grid gf, Grid gc, const T* __restrict__ f0,
                                                     const T* __restrict__ f1,
                                                     const T* __restrict__ f2, T* __restrict__ c0,
-                                                    T* __restrict__ c1, T* __restrict__ c2) {
+                                                    T* __restrict__ c1, T* __restrict__ c2, T Lc,
+                                                    unsigned char* __restrict__ flags) {
     const Span sp = tile_span(TL, gc.n0, gc.n1, gc.n2);
     const int i = sp.i, j = sp.j;
-    if (i >= gc.n0 || j >= gc.n1) return;
-    for (int k = sp.z0; k < sp.z1; ++k) {
-    const int fz = (gf.n2 > gc.n2) ? 2 : 1;
-    const int I = 2 * i, J = 2 * j, K = fz * k;
-    T s0 = T(0), s1 = T(0), s2 = T(0);
-    for (int dz = 0; dz < fz; ++dz)
-        for (int dy = 0; dy < 2; ++dy) s0 += f0[cid(gf, I, J + dy, K + dz)];
-    for (int dz = 0; dz < fz; ++dz)
-        for (int dx = 0; dx < 2; ++dx) s1 += f1[cid(gf, I + dx, J, K + dz)];
-    if (gf.ndim == 3)
-        for (int dy = 0; dy < 2; ++dy)
-            for (int dx = 0; dx < 2; ++dx) s2 += f2[cid(gf, I + dx, J + dy, K)];
-    const size_t id = cid(gc, i, j, k);
-    c0[id] = T(0.5) * s0;
-    c1[id] = T(0.5) * s1;
-    c2[id] = T(0.5) * s2;
-    }
+    bool odd = false;
+    if (i < gc.n0 && j < gc.n1)
+        for (int k = sp.z0; k < sp.z1; ++k) {
+            const int fz = (gf.n2 > gc.n2) ? 2 : 1;
+            const int I = 2 * i, J = 2 * j, K = fz * k;
+            T s0 = T(0), s1 = T(0), s2 = T(0);
+            for (int dz = 0; dz < fz; ++dz)
+                for (int dy = 0; dy < 2; ++dy) s0 += f0[cid(gf, I, J + dy, K + dz)];
+            for (int dz = 0; dz < fz; ++dz)
+                for (int dx = 0; dx < 2; ++dx) s1 += f1[cid(gf, I + dx, J, K + dz)];
+            if (gf.ndim == 3)
+                for (int dy = 0; dy < 2; ++dy)
+                    for (int dx = 0; dx < 2; ++dx) s2 += f2[cid(gf, I + dx, J + dy, K)];
+            const size_t id = cid(gc, i, j, k);
+            s0 *= T(0.5);
+            s1 *= T(0.5);
+            s2 *= T(0.5);
+            c0[id] = s0;
+            c1[id] = s1;
+            c2[id] = s2;
+            odd |= odd_face<T>(gc, i, j, k, Lc, s0, s1, s2);
+        }
+    if (flags) store_odd(odd, flags);
 }
 
 template <typename T>
@@ -1738,48 +1835,55 @@ __global__ __launch_bounds__(kBlock) void k_resid64(TileDev TL, Grid g, XAccess<
 
 // Load caller coefficients (ndim consecutive face arrays) into a level,
 // forcing zero on non-periodic lower boundary faces and on the z faces in 2D;
-// optionally keep an FP64 copy.
+// optionally keep an FP64 copy.  flags: the level's odd-face flags (those of
+// the FP64 values where a copy is kept; they cover the rounded ones').
 template <typename Tin, typename Tout>
 __global__ __launch_bounds__(kBlock) void k_load_coeffs(TileDev TL, Grid g, const Tin* __restrict__ src,
                                                         Tout* __restrict__ L0, Tout* __restrict__ L1,
                                                         Tout* __restrict__ L2, double* M0,
-                                                        double* M1, double* M2) {
+                                                        double* M1, double* M2, double Lc,
+                                                        unsigned char* __restrict__ flags) {
     const Span sp = tile_span(TL, g.n0, g.n1, g.n2);
     const int i = sp.i, j = sp.j;
-    if (i >= g.n0 || j >= g.n1) return;
-    for (int k = sp.z0; k < sp.z1; ++k) {
-    const size_t id = cid(g, i, j, k);
-    const size_t N = cells(g);
-    const int coord[3] = {i, j, k};
-    const int per[3] = {g.per0, g.per1, g.per2};
-    Tout* dst[3] = {L0, L1, L2};
-    double* d64[3] = {M0, M1, M2};
-    for (int d = 0; d < 3; ++d) {
-        double v = (d < g.ndim) ? double(src[d * N + id]) : 0.0;
-        if (!per[d] && coord[d] == 0) v = 0.0;
-        dst[d][id] = Tout(v);
-        if (d64[d]) d64[d][id] = v;
-    }
-    }
+    bool odd = false;
+    if (i < g.n0 && j < g.n1)
+        for (int k = sp.z0; k < sp.z1; ++k) {
+            const size_t id = cid(g, i, j, k);
+            const size_t N = cells(g);
+            const int coord[3] = {i, j, k};
+            const int per[3] = {g.per0, g.per1, g.per2};
+            Tout* dst[3] = {L0, L1, L2};
+            double* d64[3] = {M0, M1, M2};
+            double v[3];
+            for (int d = 0; d < 3; ++d) {
+                v[d] = (d < g.ndim) ? double(src[d * N + id]) : 0.0;
+                if (!per[d] && coord[d] == 0) v[d] = 0.0;
+                dst[d][id] = Tout(v[d]);
+                if (d64[d]) d64[d][id] = v[d];
+            }
+            odd |= odd_face<double>(g, i, j, k, Lc, v[0], v[1], v[2]);
+        }
+    store_odd(odd, flags);
 }
 
 template <typename Tin, typename Tout>
-wl_status mg_load_coeffs(const Grid& g, const Tin* src, Tout* const L[3], double* const L64[3],
-                         hipStream_t s) {
-    const Launch ln = launch_for(g.n0, g.n1, g.n2);
-    k_load_coeffs<Tin, Tout><<<ln.grid, ln.block, 0, s>>>(ln.td, g, src, L[0], L[1], L[2],
+wl_status mg_load_coeffs(Hierarchy<Tout>& h, const Tin* src, double* const L64[3], hipStream_t s) {
+    Level<Tout>& F = h.lev[0];
+    const Launch ln = launch_for(F.g.n0, F.g.n1, F.g.n2);
+    k_load_coeffs<Tin, Tout><<<ln.grid, ln.block, 0, s>>>(ln.td, F.g, src, F.L[0], F.L[1], F.L[2],
                                                           L64 ? L64[0] : nullptr,
                                                           L64 ? L64[1] : nullptr,
-                                                          L64 ? L64[2] : nullptr);
+                                                          L64 ? L64[2] : nullptr, double(F.Lc), h.odd);
     WL_CHECK_LAUNCH();
+    F.uniform = 0;
     return WL_OK;
 }
-template wl_status mg_load_coeffs<float, float>(const Grid&, const float*, float* const*,
-                                                double* const*, hipStream_t);
-template wl_status mg_load_coeffs<double, double>(const Grid&, const double*, double* const*,
-                                                  double* const*, hipStream_t);
-template wl_status mg_load_coeffs<double, float>(const Grid&, const double*, float* const*,
-                                                 double* const*, hipStream_t);
+template wl_status mg_load_coeffs<float, float>(Hierarchy<float>&, const float*, double* const*,
+                                                hipStream_t);
+template wl_status mg_load_coeffs<double, double>(Hierarchy<double>&, const double*, double* const*,
+                                                  hipStream_t);
+template wl_status mg_load_coeffs<double, float>(Hierarchy<float>&, const double*, double* const*,
+                                                 hipStream_t);
 
 template <typename T>
 wl_status fill(T* p, size_t n, T v, hipStream_t s) {
@@ -1809,10 +1913,11 @@ template wl_status convert<float, double>(const float*, double*, size_t, hipStre
 template wl_status convert<double, float>(const double*, float*, size_t, hipStream_t);
 
 // Count of active cells from FP64 coefficients (mixed-precision solver).
-wl_status mg_count_active64(const Grid& g, double* const L64[3], Reduce& red, size_t* count,
+wl_status mg_count_active64(const Grid& g, const Mixed64& m, Reduce& red, size_t* count,
                             hipStream_t s) {
     const Launch ln = launch_for(g.n0, g.n1, g.n2);
-    Coeffs<double> C{L64[0], L64[1], L64[2], 1.0};
+    Coeffs<double> C{m.L[0], m.L[1], m.L[2], 1.0};
+    C.cls = m.cls;
     k_sum_active<double, false><<<ln.grid, ln.block, 0, s>>>(ln.td, g, C, nullptr, red.partial);
     WL_CHECK_LAUNCH();
     k_reduce<<<1, 1024, 0, s>>>(red.partial, ln.nblocks(), 1, 1.0, red.result + 6, nullptr,
@@ -1864,7 +1969,7 @@ static wl_status smooth(const Level<T>& L, const T* xin, const T* b, T omega, T*
 // Fused pairs run on 3D levels whose x and y extents are multiples of 8:
 // uniform, fully periodic levels (one coefficient, w / D per level) and
 // non-uniform levels with any boundaries (per-workgroup classes; see
-// k_pair_class).  Mode 1: only levels of at least pair_min_cells() cells.
+// k_classes).  Mode 1: only levels of at least pair_min_cells() cells.
 static int pair_tx(int n0) {
     for (int w = 64; w >= 8; w >>= 1)
         if (n0 % w == 0) return w;
@@ -2156,39 +2261,65 @@ static wl_status reduce(Reduce& red, size_t nslots, int ncomp, double scale, dou
     return WL_OK;
 }
 
+// Odd-face flags of the fine coefficients that a kernel other than
+// mg_load_coeffs has written (see k_odd; of their FP64 copy where there is
+// one, whose odd faces cover the rounded ones').
+template <typename T>
+wl_status mg_flag_odd(Hierarchy<T>& h, const Mixed64* m, hipStream_t s) {
+    const Level<T>& F = h.lev[0];
+    if (F.uniform) return WL_OK;
+    const Launch ln = launch_for(F.g.n0, F.g.n1, F.g.n2);
+    if (m)
+        k_odd<double><<<ln.grid, ln.block, 0, s>>>(
+            ln.td, F.g, Coeffs<double>{m->L[0], m->L[1], m->L[2], double(F.Lc)}, h.odd);
+    else
+        k_odd<T><<<ln.grid, ln.block, 0, s>>>(ln.td, F.g, coeffs_of(F), h.odd);
+    WL_CHECK_LAUNCH();
+    return WL_OK;
+}
+template wl_status mg_flag_odd<float>(Hierarchy<float>&, const Mixed64*, hipStream_t);
+template wl_status mg_flag_odd<double>(Hierarchy<double>&, const Mixed64*, hipStream_t);
+
+// Classes of a non-uniform level's tilings from its odd-face flags.
+template <typename T>
+static wl_status level_classes(const Hierarchy<T>& h, const Level<T>& L, hipStream_t s) {
+    ClassArgs A{};
+    A.flags = A.a = launch_for(L.g.n0, L.g.n1, L.g.n2).td;
+    A.b = launch_pairs(L.g).td;
+    A.ca = L.cls;
+    A.cb = L.cls_pairs;
+    A.cp = L.cls_fp;
+    if (L.cls_fp) {
+        A.p = pair_tile(L.g);
+        A.ptx = pair_tx(L.g.n0);
+    }
+    k_classes<T><<<A.a.nb + A.b.nb + A.p.nb, kBlock, 0, s>>>(A, L.g, coeffs_of(L), h.odd);
+    WL_CHECK_LAUNCH();
+    if (L.cls_fp) {
+        k_pair_list<<<1, 1024, 0, s>>>(L.cls_fp, A.p.nb, L.fp_list);
+        WL_CHECK_LAUNCH();
+    }
+    return WL_OK;
+}
+
 template <typename T>
 wl_status mg_coarsen_all(Hierarchy<T>& h, hipStream_t s) {
+    // level by level: the odd-face flags (the fine ones are the caller's) hold
+    // for the level whose coefficients were written last
+    if (!h.lev[0].uniform) WL_TRY(level_classes(h, h.lev[0], s));
     for (int l = 1; l < h.nlev; ++l) {
         Level<T>& F = h.lev[l - 1];
         Level<T>& C = h.lev[l];
-        const Launch ln = launch_for(C.g.n0, C.g.n1, C.g.n2);
-        k_coarsen<T><<<ln.grid, ln.block, 0, s>>>(ln.td, F.g, C.g, F.L[0], F.L[1], F.L[2], C.L[0],
-                                                  C.L[1], C.L[2]);
-        WL_CHECK_LAUNCH();
         C.uniform = F.uniform;
         C.Lc = F.Lc * (F.g.ndim == 3 ? T(2) : T(1));
+        const Launch ln = launch_for(C.g.n0, C.g.n1, C.g.n2);
+        k_coarsen<T><<<ln.grid, ln.block, 0, s>>>(ln.td, F.g, C.g, F.L[0], F.L[1], F.L[2], C.L[0],
+                                                  C.L[1], C.L[2], C.Lc, C.uniform ? nullptr : h.odd);
+        WL_CHECK_LAUNCH();
+        if (!C.uniform) WL_TRY(level_classes(h, C, s));
     }
     if (const int lt = tail_level(h); lt > 0 && !h.lev[lt].uniform)
         WL_TRY(vcycle_tail(h, lt, s, true));
-    // block classes of the non-uniform levels for both tilings
-    for (int l = 0; l < h.nlev; ++l) {
-        Level<T>& L = h.lev[l];
-        if (L.uniform || !L.cls) continue;
-        const Coeffs<T> C{L.L[0], L.L[1], L.L[2], L.Lc};
-        const Launch a = launch_for(L.g.n0, L.g.n1, L.g.n2);
-        k_level_class<T><<<a.grid, a.block, 0, s>>>(a.td, L.g, C, L.cls);
-        WL_CHECK_LAUNCH();
-        const Launch b = launch_pairs(L.g);
-        k_level_class<T><<<b.grid, b.block, 0, s>>>(b.td, L.g, C, L.cls_pairs);
-        WL_CHECK_LAUNCH();
-        if (L.cls_fp) {
-            const PairTile P = pair_tile(L.g);
-            k_pair_class<T><<<P.nb, 256, 0, s>>>(P, L.g, pair_tx(L.g.n0), C, L.cls_fp);
-            WL_CHECK_LAUNCH();
-            k_pair_list<<<1, 1024, 0, s>>>(L.cls_fp, P.nb, L.fp_list);
-            WL_CHECK_LAUNCH();
-        }
-    }
     // the coarsest level's inverse on non-uniform levels, where the CG takes
     // many iterations (formed in about a fifth of a V-cycle's time,
     // recovered within a solve); on uniform ones the CG converges in a few
@@ -2245,7 +2376,8 @@ wl_status mg_count_active(Hierarchy<T>& h, Reduce& red, hipStream_t s) {
     if (F.uniform)
         k_sum_active<T, true><<<ln.grid, ln.block, 0, s>>>(ln.td, F.g, coeffs_of(F), nullptr, red.partial);
     else
-        k_sum_active<T, false><<<ln.grid, ln.block, 0, s>>>(ln.td, F.g, coeffs_of(F), nullptr, red.partial);
+        k_sum_active<T, false><<<ln.grid, ln.block, 0, s>>>(ln.td, F.g, coeffs_of(F, F.cls), nullptr,
+                                                            red.partial);
     WL_CHECK_LAUNCH();
     // result[6] = active count (kept on the device for the mean kernels)
     k_reduce<<<1, 1024, 0, s>>>(red.partial, ln.nblocks(), 1, 1.0, red.result + 6, nullptr,
@@ -2553,11 +2685,14 @@ template wl_status mg_solve<double>(Hierarchy<double>&, Reduce&, double*, const 
                                     double, int, hipStream_t, SolveResult*, BPartials,
                                     const SolveTail*);
 
-wl_status mg_mixed_classes(const Grid& g, const Mixed64& m, hipStream_t s) {
+wl_status mg_mixed_classes(const Grid& g, const Mixed64& m, const unsigned char* odd,
+                           hipStream_t s) {
     if (!m.cls) return WL_OK;
-    const Launch ln = launch_for(g.n0, g.n1, g.n2);
+    ClassArgs A{};
+    A.flags = A.a = launch_for(g.n0, g.n1, g.n2).td;
+    A.ca = m.cls;
     const Coeffs<double> C{m.L[0], m.L[1], m.L[2], 1.0};
-    k_level_class<double><<<ln.grid, ln.block, 0, s>>>(ln.td, g, C, m.cls);
+    k_classes<double><<<A.a.nb, kBlock, 0, s>>>(A, g, C, odd);
     WL_CHECK_LAUNCH();
     return WL_OK;
 }

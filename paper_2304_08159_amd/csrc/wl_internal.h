@@ -232,6 +232,9 @@ struct Hierarchy {
     int* cinv_ok = nullptr;
     bool direct_coarse = true;
     bool cinv_set = false;  // host: the flag has been set since the carve
+    // odd-face flags of the launch_for tiling of the level whose coefficients
+    // were written last (see k_classes; scratch of the coefficient set-up)
+    unsigned char* odd = nullptr;
     // V-cycle tail (non-uniform levels): w / D of its levels and their class
     // words, formed when the coefficients change
     T* tail_wd = nullptr;
@@ -360,7 +363,11 @@ struct Mixed64 {
     unsigned char* cls = nullptr;
     int inner = 3;
 };
-wl_status mg_mixed_classes(const Grid& g, const Mixed64& m, hipStream_t s);
+// (from the odd-face flags of L: before mg_coarsen_all, which takes them on)
+wl_status mg_mixed_classes(const Grid& g, const Mixed64& m, const unsigned char* odd,
+                           hipStream_t s);
+template <typename T>
+wl_status mg_flag_odd(Hierarchy<T>& h, const Mixed64* m, hipStream_t s);
 wl_status mg_solve_mixed(Hierarchy<float>& h32, const Mixed64& m, Reduce& red, double* x,
                          const double* b, double tol, double abs_r2, int max_vcycles,
                          hipStream_t s, SolveResult* res);
@@ -368,9 +375,8 @@ wl_status mg_solve_mixed(Hierarchy<float>& h32, const Mixed64& m, Reduce& red, d
 size_t reduce_slots_for(const Grid& g);
 
 template <typename Tin, typename Tout>
-wl_status mg_load_coeffs(const Grid& g, const Tin* src, Tout* const L[3], double* const L64[3],
-                         hipStream_t s);
-wl_status mg_count_active64(const Grid& g, double* const L64[3], Reduce& red, size_t* count,
+wl_status mg_load_coeffs(Hierarchy<Tout>& h, const Tin* src, double* const L64[3], hipStream_t s);
+wl_status mg_count_active64(const Grid& g, const Mixed64& m, Reduce& red, size_t* count,
                             hipStream_t s);
 template <typename T>
 wl_status fill(T* p, size_t n, T v, hipStream_t s);

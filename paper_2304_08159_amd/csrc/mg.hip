@@ -1521,7 +1521,7 @@ __global__ __launch_bounds__(kResThreads) void k_tail_classes(TailArgs<T> A) {
 // an odd-face flag per workgroup of the launch_for tiling (odd_face: a lower
 // face of its own cells that is neither), and k_classes reads coefficients
 // only where a flag is set near the workgroup.  A solve with new coefficients
-// (one sphere): 8.80 -> 8.29 ms on 256^3 cells in FP64, 9.75 -> 8.84 ms on
+// (one sphere): 8.83 -> 8.23 ms on 256^3 cells in FP64, 9.78 -> 8.66 ms on
 // 384^3 mixed.
 
 // Whether a lower face of a cell is neither Lc nor a closed domain boundary.
@@ -1588,6 +1588,8 @@ __device__ __forceinline__ AxisTiles axis_tiles(int lo, int hi, int n, int per, 
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_classes(ClassArgs A, Grid g, Coeffs<T> C,
                                                     const unsigned char* __restrict__ flags) {
+    __shared__ int found;
+    if (threadIdx.x == 0) found = 0;
     unsigned blk = blockIdx.x;
     unsigned char* cls;
     int i0, i1, j0, j1, k0, k1;  // cells [i0, i1) x [j0, j1) x [k0, k1)
@@ -1640,39 +1642,39 @@ __global__ __launch_bounds__(kBlock) void k_classes(ClassArgs A, Grid g, Coeffs<
         // cells q, q + kBlock, ... in the order x, y, z: the step as offsets
         const int sx = kBlock % wx, sy = kBlock / wx % wy, sz = kBlock / (wx * wy);
         int di = int(threadIdx.x) % wx, dj = int(threadIdx.x) / wx % wy, dk = int(threadIdx.x) / (wx * wy);
-        while (dk < wz && !odd) {
-            int i = i0 + di, j = j0 + dj, k = k0 + dk;
-            const bool ex = i == i1, ey = j == j1, ez = d3 && k == k1;
-            bool out = false;
-            if (i < 0 || i >= g.n0) {
-                out = !g.per0;
-                i = i < 0 ? i + g.n0 : i - g.n0;
+        // four cells a turn, without branches, so that their loads are in
+        // flight together (one at a time each cost a memory latency: a solve
+        // on 384^3 cells mixed 8.84 -> 8.66 ms); a cell outside reads cell 0
+        while (dk < wz && !*(volatile int*)&found) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                int i = i0 + di, j = j0 + dj, k = k0 + dk;
+                const bool fx = j != j1 && !(d3 && k == k1), fy = i != i1 && !(d3 && k == k1);
+                const bool fz = d3 && i != i1 && j != j1;
+                bool in = dk < wz;
+                const bool wi = i < 0 || i >= g.n0, wj = j < 0 || j >= g.n1, wk = d3 && (k < 0 || k >= g.n2);
+                in = in && (!wi || g.per0) && (!wj || g.per1) && (!wk || g.per2);
+                i += wi ? (i < 0 ? g.n0 : -g.n0) : 0;
+                j += wj ? (j < 0 ? g.n1 : -g.n1) : 0;
+                k += wk ? (k < 0 ? g.n2 : -g.n2) : 0;
+                const size_t id = in ? cid(g, i, j, k) : 0;
+                const T Lx = C.L0[id], Ly = C.L1[id], Lz = C.L2[id];
+                odd |= in && fx && Lx != ((i == 0 && !g.per0) ? T(0) : C.Lc);
+                odd |= in && fy && Ly != ((j == 0 && !g.per1) ? T(0) : C.Lc);
+                odd |= in && fz && Lz != ((k == 0 && !g.per2) ? T(0) : C.Lc);
+                di += sx;
+                dj += sy;
+                dk += sz;
+                if (di >= wx) {
+                    di -= wx;
+                    ++dj;
+                }
+                if (dj >= wy) {
+                    dj -= wy;
+                    ++dk;
+                }
             }
-            if (j < 0 || j >= g.n1) {
-                out = out || !g.per1;
-                j = j < 0 ? j + g.n1 : j - g.n1;
-            }
-            if (d3 && (k < 0 || k >= g.n2)) {
-                out = out || !g.per2;
-                k = k < 0 ? k + g.n2 : k - g.n2;
-            }
-            if (!out) {
-                const size_t id = cid(g, i, j, k);
-                if (!ey && !ez) odd = odd || C.L0[id] != ((i == 0 && !g.per0) ? T(0) : C.Lc);
-                if (!ex && !ez) odd = odd || C.L1[id] != ((j == 0 && !g.per1) ? T(0) : C.Lc);
-                if (d3 && !ex && !ey) odd = odd || C.L2[id] != ((k == 0 && !g.per2) ? T(0) : C.Lc);
-            }
-            di += sx;
-            dj += sy;
-            dk += sz;
-            if (di >= wx) {
-                di -= wx;
-                ++dj;
-            }
-            if (dj >= wy) {
-                dj -= wy;
-                ++dk;
-            }
+            if (odd) found = 1;  // benign race: every writer stores 1
         }
         odd = __syncthreads_or(odd ? 1 : 0) != 0;
     }

@@ -11,6 +11,7 @@ and its routines).
 """
 
 import ctypes
+import struct
 
 from . import _lib
 from ._lib import (FIELD_L0, FIELD_MU0_0, FIELD_MU1N, FIELD_P, FIELD_SIGMA, FIELD_U0,  # noqa: F401
@@ -239,28 +240,29 @@ def poisson_batch_solve(requests, allow_not_converged=False):
     count = len(requests)
     if count == 0:
         return []
+    # one pack per request (128 requests of 64 x 64 cells 2.17 -> 2.03 ms, the
+    # kernel 1.0 of them; one by one the fields of the structure took 0.6 ms)
     arr = (_lib.BatchRequest * count)()
-    dev = None
+    pack, size = _lib.BATCH_REQUEST.pack_into, _lib.BATCH_REQUEST.size
+    f64 = torch.float64
     for q, r in enumerate(requests):
         n = [int(m) for m in r["n"]]
         ndim = len(n)
         per = [int(bool(p)) for p in r.get("periodic", (False,) * ndim)]
-        for t in ("coeffs", "x", "b"):
-            ten = r[t]
-            if ten.dtype != torch.float64 or not ten.is_cuda or not ten.is_contiguous():
+        coeffs, x, b = r["coeffs"], r["x"], r["b"]
+        for t, ten in (("coeffs", coeffs), ("x", x), ("b", b)):
+            if ten.dtype != f64 or not ten.is_cuda or not ten.is_contiguous():
                 raise ValueError(f"request {q}: {t} must be a contiguous float64 CUDA tensor")
-            dev = ten.device
-        a = arr[q]
-        a.ndim = ndim
-        for i in range(3):
-            a.n[i] = (n + [1] * (3 - ndim))[i]
-            a.periodic[i] = (per + [0] * (3 - ndim))[i]
-        a.coeffs = r["coeffs"].data_ptr()
-        a.x = r["x"].data_ptr()
-        a.b = r["b"].data_ptr()
-        a.tol = float(r.get("tol", 1e-8))
-        a.max_vcycles = int(r.get("max_vcycles", 200))
-        a.mixed = int(bool(r.get("mixed", False)))
+        n += [1] * (3 - ndim)
+        per += [0] * (3 - ndim)
+        fields = (ndim, n[0], n[1], n[2], per[0], per[1], per[2], coeffs.data_ptr(), x.data_ptr(),
+                  b.data_ptr(), float(r.get("tol", 1e-8)), int(r.get("max_vcycles", 200)),
+                  int(bool(r.get("mixed", False))))
+        try:
+            pack(arr, q * size, *fields)
+        except struct.error:  # an integer beyond C's int: ctypes keeps its low bits
+            arr[q] = _lib.BatchRequest(ndim, fields[1:4], fields[4:7], *fields[7:])
+    dev = b.device
     nbytes = ctypes.c_size_t()
     check(lib.wl_poisson_batch_footprint(arr, count, ctypes.byref(nbytes)))
     ws, ptr, nb = _workspace(torch, nbytes.value, dev)

@@ -8,6 +8,7 @@ library is missing or no GPU is present, the calls raise.
 
 import ctypes
 import os
+import struct
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libwl.so")
@@ -98,6 +99,11 @@ class BatchRequest(ctypes.Structure):
     _fields_ = [("ndim", ctypes.c_int), ("n", ctypes.c_int * 3), ("periodic", ctypes.c_int * 3),
                 ("coeffs", ctypes.c_void_p), ("x", ctypes.c_void_p), ("b", ctypes.c_void_p),
                 ("tol", ctypes.c_double), ("max_vcycles", ctypes.c_int), ("mixed", ctypes.c_int)]
+
+
+# the same layout, to fill a request in one call
+BATCH_REQUEST = struct.Struct("@7i3Pd2i")
+assert BATCH_REQUEST.size == ctypes.sizeof(BatchRequest)
 
 
 class BatchResult(ctypes.Structure):

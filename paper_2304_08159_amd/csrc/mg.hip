@@ -1522,7 +1522,7 @@ __global__ __launch_bounds__(kResThreads) void k_tail_classes(TailArgs<T> A) {
 // face of its own cells that is neither), and k_classes reads coefficients
 // only where a flag is set near the workgroup.  A solve with new coefficients
 // (one sphere): 8.83 -> 8.23 ms on 256^3 cells in FP64, 9.78 -> 8.66 ms on
-// 384^3 mixed.
+// 384 x 256 x 256 mixed.
 
 // Whether a lower face of a cell is neither Lc nor a closed domain boundary.
 template <typename T>
@@ -1644,7 +1644,8 @@ __global__ __launch_bounds__(kBlock) void k_classes(ClassArgs A, Grid g, Coeffs<
         int di = int(threadIdx.x) % wx, dj = int(threadIdx.x) / wx % wy, dk = int(threadIdx.x) / (wx * wy);
         // four cells a turn, without branches, so that their loads are in
         // flight together (one at a time each cost a memory latency: a solve
-        // on 384^3 cells mixed 8.84 -> 8.66 ms); a cell outside reads cell 0
+        // on 384 x 256 x 256 cells mixed 8.84 -> 8.66 ms); a cell outside reads
+        // cell 0
         while (dk < wz && !*(volatile int*)&found) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {

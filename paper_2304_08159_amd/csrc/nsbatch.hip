@@ -8,8 +8,8 @@
 // an FP64 defect correction (Sec. 2's GMG; the mixed precision of WL_MIXED).
 // Every reduction is a fixed-order workgroup sum, so a request's result does
 // not depend on which workgroup ran it or on the rest of the batch.  The
-// per-face arithmetic (limited flux, ghost rules, BDIM blend, measure) is the
-// device code the tiled kernels use.
+// per-face arithmetic (limited flux, ghost rules, measure) is the device code
+// the tiled kernels use, the BDIM blend the same operations for a body at rest.
 #include <algorithm>
 #include <cmath>
 #include <cstring>

@@ -320,7 +320,9 @@ typedef struct {
  * request that is malformed or too large. */
 wl_status wl_poisson_batch_footprint(const wl_batch_request* reqs, int count, size_t* bytes);
 
-/* Solves count requests with one persistent kernel on hip_stream: its
+/* Solves count requests with a persistent kernel per kind of request (2D / 3D,
+ * FP64 / mixed, small / large), the first on hip_stream, further ones beside it
+ * on streams that the call forks from hip_stream and joins to it: a kernel's
  * workgroups (at most one per compute unit) take requests from a device work
  * queue until it is empty, one request per workgroup at a time.  Every
  * reduction is a fixed-order workgroup sum, so each request's result is
@@ -338,7 +340,9 @@ wl_status wl_poisson_batch_solve(const wl_batch_request* reqs, int count, void* 
  * and every request's multigrid level arrays, wl_poisson_batch_footprint
  * bytes) lives in a 32 MiB array of device memory that the library holds per
  * GPU for the life of the process; the host side uses fixed tables.  The call
- * makes no device or pinned allocation.  Limits: at most 256 requests, and a
+ * makes no device or pinned allocation; a GPU's first call with requests that
+ * take different kernels (2D / 3D, FP64 / mixed, small / large) makes up to four
+ * streams, which the process keeps.  Limits: at most 256 requests, and a
  * footprint of at most 32 MiB (e.g. 64 requests of 128^2 cells); larger
  * batches return WL_ERR_INVALID_ARG with a message naming the size.  Every
  * call on one GPU uses that GPU's single scratch array: calls that overlap on
@@ -394,9 +398,10 @@ typedef struct {
  * the first request that is malformed or too large. */
 wl_status wl_ns_batch_footprint(const wl_ns_request* reqs, int count, size_t* bytes);
 
-/* Runs count requests with one persistent kernel on hip_stream: its
- * workgroups (at most one per compute unit) take requests from a device work
- * queue until it is empty; a request's whole run is taken by one workgroup,
+/* Runs count requests with a persistent kernel per kind of request (2D / 3D,
+ * small / large; streams as in wl_poisson_batch_solve): a kernel's workgroups
+ * (at most one per compute unit) take requests from a device work queue until
+ * it is empty; a request's whole run is taken by one workgroup,
  * every phase of a step a loop over its cells followed by a barrier, every
  * reduction a fixed-order workgroup sum, so each result is bitwise
  * independent of the batch it is in.  workspace: >= the footprint, 256-byte

@@ -1402,9 +1402,10 @@ wl_status ns_momentum(const VelField<T>& E, const T* const un[3], T* const f[3],
             return WL_OK;
         }
     }
+    const dim3 grid = split_components(ln, g, allper ? kSplitCellsPeriodic : kSplitCells);
 #define WL_MOM(AP, CR)                                                                      \
-    k_momentum<T, AP, CR><<<split_components(ln, g), ln.block, 0, s>>>(ln.td, E, un[0], un[1], un[2], f[0], f[1], f[2], \
-                                                        nu, dt_dev)
+    k_momentum<T, AP, CR><<<grid, ln.block, 0, s>>>(ln.td, E, un[0], un[1], un[2], f[0], f[1], f[2], \
+                                                    nu, dt_dev)
     if (allper) {
         if (corr) WL_MOM(true, true); else WL_MOM(true, false);
     } else {

@@ -98,13 +98,19 @@ struct Launch {
 Launch launch_for(int n0, int n1, int n2);
 
 // Grid of a kernel whose components are independent, each a long serial chain
-// of loads: a workgroup per tile and component on grids of up to 2^19 cells,
-// which do not fill the chip otherwise (the per-cell momentum 36 -> 20 us at
-// 64 x 32 x 32 in FP64, 73 -> 62 us at 88 x 56 x 40, the adjoint flux gather
-// 189 -> 106 us), one per tile for all components above, where they share what
-// they load.
-inline dim3 split_components(const Launch& ln, const Grid& g) {
-    return dim3(ln.grid.x, cells(g) <= (size_t(1) << 19) ? unsigned(g.ndim) : 1u, 1);
+// of loads: a workgroup per tile and component on grids of up to `limit` cells,
+// which do not fill the chip otherwise, one per tile for all components above,
+// where they share what they load.  Both forms were timed from 2^13 to 2^19
+// cells in 2D and 3D.  With the ghost rules in the chain (walls, the adjoint's
+// gathers) the split form is 1.3 to 2.1 times as fast up to 2^17.2 cells (the
+// FP64 momentum 36 -> 17 us at 32^3), 0.98 to 1.16 times from 2^18 to 2^19
+// (momentum 57.0 -> 57.2 us at 64^3, 175 -> 151 at 80^3; the adjoint flux gather
+// 524 -> 418 at 128 x 64 x 64): 2^19.  Without them (fully periodic momentum) the chain is short:
+// 1.05 to 1.35 times up to 2^17.4, but 0.84 to 0.97 from 2^17.6 on (8.5 -> 9.8 us
+// at 512^2 in FP32, 14.0 -> 16.8 at 1024 x 512): 2^17.
+constexpr size_t kSplitCells = size_t(1) << 19, kSplitCellsPeriodic = size_t(1) << 17;
+inline dim3 split_components(const Launch& ln, const Grid& g, size_t limit = kSplitCells) {
+    return dim3(ln.grid.x, cells(g) <= limit ? unsigned(g.ndim) : 1u, 1);
 }
 
 // Number of multigrid levels: halve every active direction while all of them

@@ -1433,9 +1433,10 @@ __device__ __forceinline__ void coarse_solve_wg(const Grid& g, const T* L0, cons
 }
 
 // The coarsest solve in a launch of its own: kResThreads for the product with an
-// inverse of more than kDirectMax cells; for the iteration one wave, or 64
-// kCgGroupWaves threads (sixteen waves would only add to its barriers: 990
-// cells in FP64, 44 x 36 x 40 steps 19.6 instead of 16.6 ms).
+// inverse of more than kDirectMax cells where one was attempted; for the
+// iteration one wave, or 64 kCgGroupWaves threads (sixteen waves would only add
+// to its barriers: a solve of 510 cells in FP64 281 instead of 216 us; 990 cells,
+// 44 x 36 x 40 steps 19.6 instead of 16.6 ms).
 template <typename T>
 __global__ __launch_bounds__(kResThreads) void k_coarse_solve(
     Grid g, Coeffs<T> C, int uniform, const T* __restrict__ b, T* __restrict__ xout, double tol,
@@ -2167,7 +2168,7 @@ static wl_status coarse_solve(const Hierarchy<T>& h, const Level<T>& L, T* xout,
         return WL_ERR_INVALID_ARG;
     }
     const bool dir = h.cinv_set && &L == &h.lev[h.nlev - 1];
-    const bool product = dir && h.cinv && N > kDirectMax;
+    const bool product = dir && h.cinv_tried;
     const unsigned nt = product ? kResThreads : N <= kCgWaveMax ? 64 : 64 * kCgGroupWaves;
     k_coarse_solve<T><<<1, nt, 0, s>>>(
         L.g, coeffs_of(L), L.uniform, L.b, xout, h.coarse_tol, maxit, dir ? h.cinv : nullptr,
@@ -2323,15 +2324,24 @@ wl_status mg_coarsen_all(Hierarchy<T>& h, hipStream_t s) {
     }
     if (const int lt = tail_level(h); lt > 0 && !h.lev[lt].uniform)
         WL_TRY(vcycle_tail(h, lt, s, true));
-    // the coarsest level's inverse on non-uniform levels, where the CG takes
-    // many iterations (formed in about a fifth of a V-cycle's time,
-    // recovered within a solve); on uniform ones the CG converges in a few
-    // and keeps the solve (a cleared flag)
+    // the coarsest level's inverse: on FP64 levels of 65 to kDirectMax64 cells
+    // (k_coarse_columns), and on non-uniform ones of at most kDirectMax, where
+    // the CG takes many iterations (formed in about a fifth of a V-cycle's time,
+    // recovered within a solve); on uniform ones that small the CG converges in
+    // a few and keeps the solve (a cleared flag)
     if (h.cinv) {
         const Level<T>& Cst = h.lev[h.nlev - 1];
         const size_t N = cells(Cst.g);
         const bool direct = h.direct_coarse && direct_coarse_enabled();
-        if (direct && N > size_t(kDirectMax)) {
+        // (the coarsest solve's workgroup follows from it: captured bodies that
+        // hold the other one are dropped)
+        const bool tried = direct && N > size_t(kDirectMax);
+        if (tried != h.cinv_tried) {
+            WL_CHECK_HIP(hipStreamSynchronize(s));
+            h.graphs.clear();
+            h.cinv_tried = tried;
+        }
+        if (tried) {
             if constexpr (sizeof(T) == 8) {
                 k_fill<int><<<1, 64, 0, s>>>(h.cinv_ok, 1, 1);
                 WL_CHECK_LAUNCH();

@@ -238,6 +238,7 @@ struct Hierarchy {
     int* cinv_ok = nullptr;
     bool direct_coarse = true;
     bool cinv_set = false;  // host: the flag has been set since the carve
+    bool cinv_tried = false;  // host: an inverse of more than kDirectMax cells was attempted
     // odd-face flags of the launch_for tiling of the level whose coefficients
     // were written last (see k_classes; scratch of the coefficient set-up)
     unsigned char* odd = nullptr;

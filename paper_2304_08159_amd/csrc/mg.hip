@@ -1374,9 +1374,9 @@ __global__ __launch_bounds__(64 * kCgGroupWaves) void k_coarse_columns(Grid g, C
     const int N = int(cells(g)), j = int(blockIdx.x);
     for (int c = int(threadIdx.x); c < N; c += int(blockDim.x)) e[c] = c == j ? 1.0 : 0.0;
     __syncthreads();
-    const bool done = coarse_cg<double, 2, false>(g, C.L0, C.L1, C.L2, C.Lc, uniform, e,
-                                                  G + size_t(j) * N, 1e-13, 2 * N + 64, S);
-    if (!done && threadIdx.x == 0) *ok = 0;
+    const bool reached = coarse_cg<double, 2, false>(g, C.L0, C.L1, C.L2, C.Lc, uniform, e,
+                                                     G + size_t(j) * N, 1e-13, 2 * N + 64, S);
+    if (!reached && threadIdx.x == 0) *ok = 0;
 }
 
 // x = b G by every thread of a workgroup of kResThreads: lane i of part p sums

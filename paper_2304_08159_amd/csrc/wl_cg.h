@@ -77,7 +77,8 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 
 // WAVE: called by the first wave alone; else by every thread of the workgroup
 // (at least 64 nw), the waves beyond nw only meeting the barriers.
-// Returns whether the residual reached the tolerance.
+// Returns whether the residual reached the tolerance (a residual that is no
+// number ends the iteration without having reached it).
 template <typename T, int PER, bool WAVE>
 __device__ __forceinline__ bool coarse_cg(const Grid& g, const T* L0, const T* L1, const T* L2,
                                           T Lc, int uniform, const T* b, T* xout, double tol,
@@ -178,7 +179,7 @@ __device__ __forceinline__ bool coarse_cg(const Grid& g, const T* L0, const T* L
     }
     publish();
     double goal = 0.0, inv_rr0 = 0.0, pq = 0.0;
-    bool done = false;
+    bool reached = false;
     for (int it = 0; it <= maxit; ++it) {
         double rr = 0.0, rw = 0.0;
 #pragma unroll
@@ -194,9 +195,9 @@ __device__ __forceinline__ bool coarse_cg(const Grid& g, const T* L0, const T* L
             rw = fma(r[m], v, rw);
         }
         sums(rr, rw);
-        // converged (or zero from the start), or out of iterations
-        done = !(rr > goal);
-        if (done || it == maxit) break;
+        // converged (or zero from the start), not a number, or out of iterations
+        reached = rr <= goal;
+        if (!(rr > goal) || it == maxit) break;
         if (it == 0) goal = tol * tol * rr;
         const double beta = rr * inv_rr0;            // 0 at first
         pq = fma(-beta * beta, pq, rw);              // p M p = r w - beta^2 (p M p before)
@@ -223,7 +224,7 @@ __device__ __forceinline__ bool coarse_cg(const Grid& g, const T* L0, const T* L
 #pragma unroll
     for (int m = 0; m < PER; ++m)
         if (own[m]) xout[t + stride * m] = act[m] ? T(x[m] - xm) : T(0);
-    return done;
+    return reached;
 }
 
 // The iterative coarsest solve of a workgroup of at least 512 threads (every

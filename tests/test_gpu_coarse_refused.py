@@ -1,5 +1,6 @@
 """Coarsest levels that have room for an inverse but are solved by the
-iteration."""
+iteration: no inverse attempted, or one refused because a row of it did not
+converge."""
 
 import time
 
@@ -51,3 +52,12 @@ def test_iteration_without_an_inverse_runs_at_its_own_workgroup(monkeypatch):
     beyond, within = _time(*_solver((171, 3))), _time(*_solver((170, 3)))
     print("513 cells", round(beyond, 1), "us, 510 cells", round(within, 1), "us", flush=True)
     assert within <= 1.05 * beyond
+
+
+def test_rows_that_are_no_numbers_are_refused():
+    """Coefficients of 1e-310: a unit row divides by them and ends in NaN.  The
+    iteration on a right-hand side of 1e-155 finds no descent (its products
+    underflow) and leaves the zero correction."""
+    ps, L, b = _solver((12, 11))
+    x = _solve(ps, 1e-310 * L, 1e-155 * b)
+    assert bool(torch.isfinite(x).all())

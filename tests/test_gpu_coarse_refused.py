@@ -61,3 +61,89 @@ def test_rows_that_are_no_numbers_are_refused():
     ps, L, b = _solver((12, 11))
     x = _solve(ps, 1e-310 * L, 1e-155 * b)
     assert bool(torch.isfinite(x).all())
+
+
+def _cell_faces(L, cell, value):
+    """The faces of one cell, (i, j) or (i, j, k), set to value."""
+    d = len(cell)
+    for i in range(d):
+        at = [0] * (3 - d) + list(reversed(cell))
+        L[(i, *at)] = value
+        at[2 - i] += 1
+        L[(i, *at)] = value
+
+
+def _cut(L, plane):
+    """The lower x faces of a plane closed: the box in two parts."""
+    L[0, :, :, plane] = 0.0
+
+
+def _residual(L, x, b):
+    r = b.clone()
+    for i in range(L.shape[0]):
+        f = L[i] * (x - torch.roll(x, 1, 2 - i))
+        r += f - torch.roll(f, -1, 2 - i)
+    return float(r.norm() / b.norm())
+
+
+def _parts(b, plane):
+    """b without its mean on either side of the plane."""
+    b = b.clone()
+    for part in (b[..., :plane], b[..., plane:]):
+        part -= part.mean()
+    return b
+
+
+# 77 and 385 cells (two group sizes), the largest level with an inverse
+@pytest.mark.parametrize("n", [(11, 7), (11, 7, 5), (32, 16)], ids=["77", "385", "512"])
+@pytest.mark.parametrize("kind", ["cut", 1e-7, 1e-9, 1e-12])
+def test_refused_inverse_leaves_the_iteration(n, kind, monkeypatch):
+    """Two parts, or faces so small that rows do not converge: bit for bit the
+    solve without an inverse."""
+    ps, L, b = _solver(n)
+    if kind == "cut":
+        _cut(L, 4)
+        b = _parts(b, 4)
+    else:
+        _cell_faces(L, tuple(m // 2 for m in n), kind)
+        at = (0,) * (3 - len(n)) + tuple(m // 2 for m in reversed(n))
+        b[at] = 0.0
+        b -= b.sum() / (b.numel() - 1)
+        b[at] = 0.0
+    x = _solve(ps, L, b)
+    monkeypatch.setenv("WL_DIRECT_COARSE", "0")
+    y = _solve(ps, L, b)
+    assert torch.equal(x, y)
+    # the iteration's tolerance and the rounding of A x
+    assert _residual(L, x, b) <= 1.1e-10
+
+
+@pytest.mark.parametrize("kind", [1e-2, 1e-4])
+def test_inverse_with_a_narrow_cell_meets_the_iterations_tolerance(kind, monkeypatch):
+    ps, L, b = _solver((11, 7, 5))
+    _cell_faces(L, (5, 3, 2), kind)
+    x = _solve(ps, L, b)
+    monkeypatch.setenv("WL_DIRECT_COARSE", "0")
+    assert not torch.equal(x, _solve(ps, L, b))  # the inverse was taken
+    # rows to 1e-13 of unit vectors, 385 of them: within the iteration's 1e-10
+    assert _residual(L, x, b) <= 1e-10
+
+
+def test_one_handle_forms_and_refuses_in_turn(monkeypatch):
+    """The flag, the launch and the captured bodies follow the coefficients and
+    the switch: each solve equals that of a handle which never saw another."""
+    n = (11, 7, 5)
+    ps, L, b = _solver(n)
+    C = L.clone()
+    _cut(C, 4)
+    bc = _parts(b, 4)
+    runs = [(L, b, "1"), (C, bc, "1"), (L, b, "0"), (L, b, "1"), (C, bc, "0"), (L, b, "1")]
+    for coeffs, rhs, switch in runs:
+        monkeypatch.setenv("WL_DIRECT_COARSE", switch)
+        fresh = _solver(n)[0]
+        want = _solve(fresh, coeffs, rhs)
+        for _ in range(3):  # the third replays a captured body
+            assert torch.equal(_solve(ps, coeffs, rhs), want)
+            x = torch.zeros_like(rhs)
+            ps.solve(None, x, rhs, tol=0.0, max_vcycles=1, allow_not_converged=True)
+            assert torch.equal(x, want)

@@ -579,6 +579,7 @@ wl_status wl_poisson_batch_solve(const wl_batch_request* reqs, int count, void* 
     if (count == 0) return WL_OK;
     if (!workspace || !results) return set_error("workspace / results is NULL"), WL_ERR_INVALID_ARG;
     if (count < 0) return set_error("count must be >= 0"), WL_ERR_INVALID_ARG;
+    if (!reqs) return set_error("reqs is NULL"), WL_ERR_INVALID_ARG;
     std::vector<BatchReq> table(static_cast<size_t>(count));
     std::vector<BatchRes> res(static_cast<size_t>(count));
     std::vector<int> place(static_cast<size_t>(count));

@@ -592,6 +592,7 @@ wl_status wl_ns_batch_run(const wl_ns_request* reqs, int count, void* workspace,
     clear_error();
     if (count == 0) return WL_OK;
     if (count < 0) return set_error("count must be >= 0"), WL_ERR_INVALID_ARG;
+    if (!reqs) return set_error("reqs is NULL"), WL_ERR_INVALID_ARG;
     if (!workspace || !results) return set_error("workspace / results is NULL"), WL_ERR_INVALID_ARG;
     if (reinterpret_cast<uintptr_t>(workspace) % 256)
         return set_error("workspace must be 256-byte aligned"), WL_ERR_INVALID_ARG;

@@ -230,7 +230,7 @@ void carve_hierarchy(Carver& c, Hierarchy<T>& h, int ndim, const int n[3], const
     const size_t Nc = cells(h.lev[nlev - 1].g);
     if (Nc <= size_t(sizeof(T) == 8 ? kDirectMax64 : kDirectMax)) {
         h.cinv = c.take<double>(Nc * Nc);
-        h.cinv_ok = c.take<int>(1);
+        h.cinv_ok = c.take<int>(2);  // within the 256 bytes one takes
     }
 }
 
@@ -1360,11 +1360,66 @@ __device__ void coarse_direct_wave(const Grid& g, const T* L0, const T* L1, cons
 // FP64 coarsest levels of 65 to kDirectMax64 cells: row j of G is the
 // minimum-norm solution for the unit right-hand side e_j, all rows at once, one
 // workgroup each, by the iteration itself run to a residual of 1e-13; a row
-// that does not get there (disconnected active cells) clears *ok and the
-// iteration solves instead.  385 cells past a sphere: formed in 0.1 ms, and a
-// solve is one product (coarse_direct_wg) instead of about a hundred dependent
-// iterations (62 us).  FP32 levels keep the iteration: what its tolerance leaves
-// in the weak modes of nearly closed cells is part of their results.
+// that does not get there clears *ok and the iteration solves instead.  385 cells
+// past a sphere: formed in 0.1 ms, and a solve is one product (coarse_direct_wg)
+// instead of about a hundred dependent iterations (62 us); uniform levels gain
+// as well (four periodic steps with 125 coarsest cells 5.10 -> 4.98 ms, 216 5.91
+// -> 5.28, 441 9.32 -> 8.60).  FP32 levels keep the iteration: what its tolerance
+// leaves in the weak modes of nearly closed cells is part of their results.
+//
+// Rows fail where the active cells are in several parts, and where a body nearly
+// closes a cell: some always do with the cell's faces below 5e-7 of the others'
+// (kNarrow; in an emulation over levels of 72 to 512 cells), hardly any above
+// 1e-5.  A refused attempt is lost, so a cell below kNarrow refuses it before any
+// iteration (k_coarse_narrow), and a row gets no more iterations than rows that
+// converge were seen to take (columns_maxit: at most 166 on levels of up to 504
+// cells past spheres, 351 on 256 x 2).  Two of 14 spheres placed at random in
+// 88 x 56 x 40 cells are refused: one V-cycle with the coefficients of the
+// narrower one 1.06 -> 0.42 ms (without the attempt 0.41; each row had run for
+// 2 N + 64 iterations), a whole solve 4.31 -> 3.69 and 4.02 -> 3.72 ms.  An
+// accepted inverse is recovered within two V-cycles (504 cells: one V-cycle 0.36
+// ms without, 0.39 with, twelve 2.16 and 1.56).
+constexpr double kNarrow = 5e-7;
+static int columns_maxit(const Grid& g) {
+    const int N = int(cells(g));
+    return std::max(N / 2 + 64, 2 * std::max(g.n0, std::max(g.n1, g.n2)));
+}
+
+// ok[0], whether no cell is narrower than kNarrow, and ok[1], the rows'
+// iterations (none where one is).  One workgroup.
+__global__ __launch_bounds__(kDirectMax64) void k_coarse_narrow(Grid g, Coeffs<double> C,
+                                                                int uniform, int maxit,
+                                                                int* __restrict__ ok) {
+    __shared__ double red[2 * kDirectMax64 / 64];
+    const int N = int(cells(g)), t = int(threadIdx.x);
+    double hi = 0.0, lo = INFINITY;  // the largest and the smallest positive diagonal
+    if (t < N && !uniform) {
+        double xI, Ax, D;
+        apply_row<double, XM_ZERO, false>(g, XAccess<double, XM_ZERO>{nullptr}, C, t % g.n0,
+                                          t / g.n0 % g.n1, t / (g.n0 * g.n1), xI, Ax, D);
+        hi = D;
+        if (D > 0.0) lo = D;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        hi = fmax(hi, __shfl_xor(hi, off, 64));
+        lo = fmin(lo, __shfl_xor(lo, off, 64));
+    }
+    if ((t & 63) == 0) {
+        red[2 * (t >> 6)] = hi;
+        red[2 * (t >> 6) + 1] = lo;
+    }
+    __syncthreads();
+    if (t != 0) return;
+    for (int w = 1; w < kDirectMax64 / 64; ++w) {
+        hi = fmax(hi, red[2 * w]);
+        lo = fmin(lo, red[2 * w + 1]);
+    }
+    const bool narrow = lo < kNarrow * hi;
+    ok[0] = narrow ? 0 : 1;
+    ok[1] = narrow ? 0 : maxit;
+}
+
 __global__ __launch_bounds__(64 * kCgGroupWaves) void k_coarse_columns(Grid g, Coeffs<double> C,
                                                                        int uniform,
                                                                        double* __restrict__ G,
@@ -1372,10 +1427,11 @@ __global__ __launch_bounds__(64 * kCgGroupWaves) void k_coarse_columns(Grid g, C
     __shared__ CgLds S;
     __shared__ double e[kDirectMax64];
     const int N = int(cells(g)), j = int(blockIdx.x);
+    const int maxit = __builtin_amdgcn_readfirstlane(ok[1]);
     for (int c = int(threadIdx.x); c < N; c += int(blockDim.x)) e[c] = c == j ? 1.0 : 0.0;
     __syncthreads();
     const bool reached = coarse_cg<double, 2, false>(g, C.L0, C.L1, C.L2, C.Lc, uniform, e,
-                                                     G + size_t(j) * N, 1e-13, 2 * N + 64, S);
+                                                     G + size_t(j) * N, 1e-13, maxit, S);
     if (!reached && threadIdx.x == 0) *ok = 0;
 }
 
@@ -2343,7 +2399,8 @@ wl_status mg_coarsen_all(Hierarchy<T>& h, hipStream_t s) {
         }
         if (tried) {
             if constexpr (sizeof(T) == 8) {
-                k_fill<int><<<1, 64, 0, s>>>(h.cinv_ok, 1, 1);
+                k_coarse_narrow<<<1, kDirectMax64, 0, s>>>(Cst.g, coeffs_of(Cst), Cst.uniform,
+                                                           columns_maxit(Cst.g), h.cinv_ok);
                 WL_CHECK_LAUNCH();
                 k_coarse_columns<<<unsigned(N), unsigned(64 * ((N + 127) / 128)), 0, s>>>(
                     Cst.g, coeffs_of(Cst), Cst.uniform, h.cinv, h.cinv_ok);

@@ -1488,16 +1488,19 @@ __device__ __forceinline__ void coarse_solve_wg(const Grid& g, const T* L0, cons
     coarse_cg_wg<T>(g, L0, L1, L2, Lc, uniform, b, xout, tol, maxit, S);
 }
 
-// The coarsest solve in a launch of its own: kResThreads for the product with an
-// inverse of more than kDirectMax cells where one was attempted; for the
-// iteration one wave, or 64 kCgGroupWaves threads (sixteen waves would only add
-// to its barriers: a solve of 510 cells in FP64 281 instead of 216 us; 990 cells,
-// 44 x 36 x 40 steps 19.6 instead of 16.6 ms).
+// The coarsest solve in a launch of its own: kResThreads where the product with
+// an inverse of more than kDirectMax cells may be taken, else one wave, or 64
+// kCgGroupWaves threads.  Where the product is not taken (no inverse formed, or
+// one refused) the waves that the iteration does not want end at once; the
+// others' barriers do not wait for waves that have ended.  Sixteen waves would
+// only add to them: a solve of 510 cells in FP64 281 instead of 216 us; 990 cells,
+// 44 x 36 x 40 steps 19.6 instead of 16.6 ms.
 template <typename T>
 __global__ __launch_bounds__(kResThreads) void k_coarse_solve(
     Grid g, Coeffs<T> C, int uniform, const T* __restrict__ b, T* __restrict__ xout, double tol,
     int maxit, const double* G, const int* ok) {
     __shared__ CgLds S;
+    if (threadIdx.x >= 64 * kCgGroupWaves && *ok == 0) return;
     coarse_solve_wg<T>(g, C.L0, C.L1, C.L2, C.Lc, uniform, b, xout, tol, maxit, G, ok, S);
 }
 
@@ -2224,7 +2227,7 @@ static wl_status coarse_solve(const Hierarchy<T>& h, const Level<T>& L, T* xout,
         return WL_ERR_INVALID_ARG;
     }
     const bool dir = h.cinv_set && &L == &h.lev[h.nlev - 1];
-    const bool product = dir && h.cinv_tried;
+    const bool product = dir && h.cinv && N > kDirectMax;
     const unsigned nt = product ? kResThreads : N <= kCgWaveMax ? 64 : 64 * kCgGroupWaves;
     k_coarse_solve<T><<<1, nt, 0, s>>>(
         L.g, coeffs_of(L), L.uniform, L.b, xout, h.coarse_tol, maxit, dir ? h.cinv : nullptr,
@@ -2389,15 +2392,7 @@ wl_status mg_coarsen_all(Hierarchy<T>& h, hipStream_t s) {
         const Level<T>& Cst = h.lev[h.nlev - 1];
         const size_t N = cells(Cst.g);
         const bool direct = h.direct_coarse && direct_coarse_enabled();
-        // (the coarsest solve's workgroup follows from it: captured bodies that
-        // hold the other one are dropped)
-        const bool tried = direct && N > size_t(kDirectMax);
-        if (tried != h.cinv_tried) {
-            WL_CHECK_HIP(hipStreamSynchronize(s));
-            h.graphs.clear();
-            h.cinv_tried = tried;
-        }
-        if (tried) {
+        if (direct && N > size_t(kDirectMax)) {
             if constexpr (sizeof(T) == 8) {
                 k_coarse_narrow<<<1, kDirectMax64, 0, s>>>(Cst.g, coeffs_of(Cst), Cst.uniform,
                                                            columns_maxit(Cst.g), h.cinv_ok);

@@ -102,12 +102,13 @@ Launch launch_for(int n0, int n1, int n2);
 // which do not fill the chip otherwise, one per tile for all components above,
 // where they share what they load.  Both forms were timed from 2^13 to 2^19
 // cells in 2D and 3D.  With the ghost rules in the chain (walls, the adjoint's
-// gathers) the split form is 1.3 to 2.1 times as fast up to 2^17.2 cells (the
-// FP64 momentum 36 -> 17 us at 32^3), 0.98 to 1.16 times from 2^18 to 2^19
-// (momentum 57.0 -> 57.2 us at 64^3, 175 -> 151 at 80^3; the adjoint flux gather
-// 524 -> 418 at 128 x 64 x 64): 2^19.  Without them (fully periodic momentum) the chain is short:
-// 1.05 to 1.35 times up to 2^17.4, but 0.84 to 0.97 from 2^17.6 on (8.5 -> 9.8 us
-// at 512^2 in FP32, 14.0 -> 16.8 at 1024 x 512): 2^17.
+// gathers) the split form is as fast or faster: the momentum 1.1 to 2.1 times up
+// to 2^17.2 cells (FP64, 32^3: 36 -> 17 us), 0.98 to 1.16 times from 2^18 to 2^19
+// (64^3 57.0 -> 57.2, 80^3 175 -> 151); the adjoint's flux gather 1.02 to 2.4
+// times throughout (FP64, 128 x 64 x 64: 542 -> 438), periodic or not: 2^19.  The
+// fully periodic momentum is a short chain: 1.0 to 1.35 times up to 2^17.4, but
+// 0.84 to 0.97 from 2^17.6 on (FP32, 512^2: 8.5 -> 9.8 us; 1024 x 512: 14.0 ->
+// 16.8): 2^17.
 constexpr size_t kSplitCells = size_t(1) << 19, kSplitCellsPeriodic = size_t(1) << 17;
 inline dim3 split_components(const Launch& ln, const Grid& g, size_t limit = kSplitCells) {
     return dim3(ln.grid.x, cells(g) <= limit ? unsigned(g.ndim) : 1u, 1);
@@ -238,7 +239,6 @@ struct Hierarchy {
     int* cinv_ok = nullptr;
     bool direct_coarse = true;
     bool cinv_set = false;  // host: the flag has been set since the carve
-    bool cinv_tried = false;  // host: an inverse of more than kDirectMax cells was attempted
     // odd-face flags of the launch_for tiling of the level whose coefficients
     // were written last (see k_classes; scratch of the coefficient set-up)
     unsigned char* odd = nullptr;

@@ -228,7 +228,8 @@ class Sim:
 
 
 def poisson_batch_solve(requests, allow_not_converged=False):
-    """Solve many small Poisson problems with one persistent kernel.
+    """Solve many small Poisson problems with persistent kernels, one per kind
+    of request, side by side.
 
     requests: list of dicts with n (2 or 3 ints), periodic, coeffs (float64
     tensor (ndim, n2, n1, n0)), x (float64, guess in / solution out), b
@@ -312,7 +313,7 @@ def ns_batch_footprint(requests):
 
 
 def ns_batch_run(requests, allow_not_converged=False):
-    """Run many small simulations with one persistent kernel (FP32 fields,
+    """Run many small simulations with persistent kernels (FP32 fields,
     mixed-precision solves to a relative residual).
 
     requests: list of dicts with n, bc_lo, bc_hi, U, nu, body (at rest; may be

@@ -766,6 +766,8 @@ __global__ __launch_bounds__(kBlock) void k_flag_list(size_t n, const unsigned c
     if (on) list[at + unsigned(__popcll(m & ((1ull << lane) - 1ull)))] = unsigned(id);
 }
 
+// Tile class of each block: 1 if any face of its tile has mu0 != 1 or a
+// nonzero mu1 n component.  cflag (may be null): the same per cell.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_tile_class(TileDev TL, Grid g, BdimFields<T> B,
                                                        unsigned char* __restrict__ cls,

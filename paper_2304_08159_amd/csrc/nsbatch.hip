@@ -1,5 +1,6 @@
 // Batched Navier-Stokes runs for serving many small simulations: one
-// persistent kernel whose workgroups take requests from a device work queue
+// persistent kernel per kind of request (pressure solves resident in 2D, in 3D, or
+// not) whose workgroups take requests from a device work queue
 // (an atomic head over the request table) until it is empty.  A request is a
 // whole run of `steps` CFL-adaptive Heun steps (Sec. 3's simstep!) taken by
 // the one workgroup that took it: every phase of the step (CFL!, convdiff!,

@@ -25,7 +25,8 @@
 // (resid_row and its order of sums over the 2^d children) and k_prolong: the
 // V-cycle tail's iterates are bitwise those of the per-level kernels.  RS_SEQ is
 // that of wl_wg.h (w r / D, children summed one after another): the batched
-// solvers' iterates are bitwise those of their general path.
+// mixed-precision solves take it, and their iterates are bitwise those of their
+// general path.  (The batched FP64 solves take RS_TILED, see res_solve64.)
 #pragma once
 
 #include <type_traits>

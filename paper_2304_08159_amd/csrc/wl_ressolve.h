@@ -120,10 +120,12 @@ __device__ __forceinline__ double res_project(const RLevel<double>& L, const uns
     return wg_sum(b2, red);
 }
 
-// FP64 V-cycles (RS_TILED: one fused multiply-add where RS_SEQ divides; the
-// results differ from the general path's by rounding, 1e-17 of their norm) on
-// A x = b_in until ||r|| <= tol ||b||; x and b (scratch) in global memory.  As solve_one's general path, with the norm taken by the
-// first pre-smoothing sweep of the next V-cycle.
+// FP64 V-cycles on A x = b_in until ||r|| <= tol ||b||; x and b (scratch) in
+// global memory.  As solve_one's general path, with the norm taken by the first
+// pre-smoothing sweep of the next V-cycle, and in the RS_TILED style: one fused
+// multiply-add where RS_SEQ divides, the children summed pair by pair.  The
+// solutions differ from the general path's by rounding: 2e-18 (128^2) to 2e-15
+// (90 x 44) of their norm over seven sizes in 2D and 3D, after the same V-cycles.
 template <bool D3>
 __device__ __forceinline__ void res_solve64(const ResPlan64& P, double omega, const double* b_in,
                                             double* xg, double* b, double tol, int max_vcycles,

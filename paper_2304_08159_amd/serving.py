@@ -12,7 +12,7 @@ beside it (checked bitwise by the tests through result fingerprints).
 Small requests are batched: when one of them is admitted, the dispatcher
 gathers further waiting small requests of the same kind (FIFO, up to
 `batch_max`, within the free budget) into the same unit, which the executor
-runs with one persistent work-queue kernel whose workgroups take requests
+runs with persistent work-queue kernels whose workgroups take requests
 from a device queue, one request per workgroup at a time: Poisson solves
 (`wl_poisson_batch_solve`, FP32 V-cycles with FP64 defect correction) or
 whole Navier-Stokes runs (`wl_ns_batch_run`, FP32 fields, mixed-precision
@@ -257,12 +257,11 @@ class GpuExecutor(Executor):
     is an exact integer hash of the output bits."""
 
     # Batching limits from measured latencies of one request (MI355X): a
-    # Poisson solve takes 1.8-2.1 ms on the whole GPU at every size of the
-    # mix and 1.4 / 2.6 / 7.7 / 46 ms as one workgroup of the persistent
-    # kernel at 64^2 / 128^2 / 256^2 / 64^3; a 20-step NS run 35 / 41 / 48 ms
-    # alone and 49 / 140 / 538 ms in one workgroup at 64^2 / 128^2 / 256^2.
-    # Kinds are batched only where one workgroup stays within about 1.5x of
-    # the whole-GPU latency.
+    # Poisson solve takes 1.0 / 1.0 / 1.4 / 1.5 ms on the whole GPU and 0.5 /
+    # 0.9 / 7.4 / 46 ms as one workgroup of a persistent kernel at 64^2 / 128^2 /
+    # 256^2 / 64^3; a 20-step NS run 19 / 24 / 30 ms alone and 18 / 114 / 438 ms
+    # in one workgroup at 64^2 / 128^2 / 256^2.  Kinds are batched only where one
+    # workgroup stays within about 1.5x of the whole-GPU latency.
     def __init__(self, device="cuda", keep_fields=False, batch_cells=16384,
                  ns_batch_cells=4096):
         import torch
@@ -372,7 +371,7 @@ class GpuExecutor(Executor):
         return u, uout, p
 
     def run_ns_batch(self, rs):
-        """Small NS requests through one persistent kernel (a whole run per
+        """Small NS requests through persistent kernels (a whole run per
         workgroup).  With keep_fields the last step runs as a launch of its
         own, so that the state before it is kept for replays (same bits)."""
         torch, wl = self.torch, self.wl
@@ -410,9 +409,9 @@ class GpuExecutor(Executor):
 
     def run_batch(self, rs):
         """Small Poisson requests (Neumann box, centred sphere / circle, N(0,1)
-        right-hand side; FP32 V-cycles with FP64 defect correction) through one
-        persistent work-queue kernel; small NS requests through the batched
-        NS kernel."""
+        right-hand side; FP32 V-cycles with FP64 defect correction) through
+        persistent work-queue kernels; small NS requests through the batched
+        NS kernels."""
         if rs and rs[0].kind == "ns":
             return self.run_ns_batch(rs)
         torch, wl = self.torch, self.wl
